@@ -330,6 +330,21 @@ fw2_status transfer_fields(fw2_domain *d, uint32_t mask, void *buf, int32_t kind
                                                : (to_device ? hipMemcpyHostToDevice : hipMemcpyDeviceToHost);
     const fw2::Geometry &g = d->ly.geo;
     const int nd = g.ndim, L = d->desc.n_relax;
+    if (kind == FW2_DEVICE && (uintptr_t)buf % 4 == 0) {   // one launch moves every selected array
+        const fw2::StepArgs &a = d->args;
+        fw2::PlaneSet s;
+        std::memset(&s, 0, sizeof(s));
+        if (mask & FW2_FIELD_P) s.add(a.p, 0, g.n[2]);
+        if (mask & FW2_FIELD_V) s.add(a.v, 0, g.n[2], nd, 1);
+        if (mask & FW2_FIELD_PSI1) s.add(a.psi1, 0, g.n[2], nd * L, L);
+        if (mask & FW2_FIELD_PSI2) s.add(a.psi2, 0, g.n[2], nd * L);
+        if (to_device)
+            FW2_HIP(fw2::launch_unpack(s, g, (const float *)buf, d->stream));
+        else
+            FW2_HIP(fw2::launch_pack(s, g, (float *)buf, d->stream));
+        FW2_HIP(hipStreamSynchronize(d->stream));
+        return FW2_OK;
+    }
     const size_t field_b = (size_t)d->npts() * 4;
     char *cur = (char *)buf;
     FW2_HIP(hipStreamSynchronize(d->stream));
@@ -374,12 +389,7 @@ fw2::PlaneSet halo_planes(const fw2_domain *d, int kind, int side, bool unpack)
     auto add = [&](const float *arr, int count) {
         // low side: planes [0, count) packed, [-count, 0) unpacked;
         // high side: [nz - count, nz) packed, [nz, nz + count) unpacked
-        const int z0 = side == FW2_LOW ? (unpack ? -count : 0) : (unpack ? nz : nz - count);
-        s.arr[s.n] = arr;
-        s.z0[s.n] = z0;
-        s.nz[s.n] = count;
-        s.total += count;
-        s.n++;
+        s.add(arr, side == FW2_LOW ? (unpack ? -count : 0) : (unpack ? nz : nz - count), count);
     };
     if (kind == FW2_HALO_P) {
         add(a.p, fw2::kHalo);

@@ -183,15 +183,33 @@ hipError_t launch_fill(float *dst, int64_t n, float value, hipStream_t stream);
 hipError_t launch_check(const float *p, const Geometry &g, float limit, int *flag, hipStream_t stream);
 hipError_t launch_set_counter(long long *counter, long long value, hipStream_t stream);
 
-// Halo planes of a slab (halo.hip).  A plane set lists `n` (array, first
-// plane, plane count) ranges; pack gathers their unpadded [ny][nx] planes in
-// order into dst, unpack scatters src back into the same planes.
+// Planes packed or unpacked in one launch (halo.hip): the halo planes of a
+// slab, or whole fields (fw2_read_fields / fw2_write_fields with device
+// memory).  A set lists `n` ranges, each of `reps` consecutive arrays (one
+// stride apart) from arr with planes [z0, z0 + nz); pack gathers their
+// unpadded [ny][nx] planes in order into dst, unpack scatters src back into
+// the same planes.  per_axis > 0 marks velocity points: array r of the range
+// belongs to axis r / per_axis, and an unpack leaves out its last sample
+// along that axis (outside the grid, held at zero).
 struct PlaneSet {
     const float *arr[4];
     int32_t z0[4];
     int32_t nz[4];
+    int32_t reps[4];
+    int32_t per_axis[4];
     int32_t n;
-    int32_t total;           // sum of nz
+    int32_t total;           // planes: sum of nz * reps
+
+    void add(const float *a, int first, int count, int arrays = 1, int arrays_per_axis = 0)
+    {
+        arr[n] = a;
+        z0[n] = first;
+        nz[n] = count;
+        reps[n] = arrays;
+        per_axis[n] = arrays_per_axis;
+        total += count * arrays;
+        n++;
+    }
 };
 hipError_t launch_pack(const PlaneSet &s, const Geometry &g, float *dst, hipStream_t stream);
 hipError_t launch_unpack(const PlaneSet &s, const Geometry &g, const float *src, hipStream_t stream);

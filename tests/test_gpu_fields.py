@@ -1,0 +1,45 @@
+"""Packed fields through device memory (one launch for every selected array)
+against the same call on host memory (a row copy per plane): equal values."""
+import numpy as np
+import pytest
+
+import workloads as W
+from paper_2106_11476_amd import fw2
+
+pytestmark = pytest.mark.gpu
+
+# multiples of four (four values a thread), remainders, single columns and rows
+SHAPES = [(64, 12), (5, 9), (1, 7), (8, 1), (260, 3), (12, 6, 5), (7, 5, 3), (4, 1, 6), (66, 4, 1)]
+
+
+def _domain(shape, L):
+    prob = W.homogeneous(shape, L=L)
+    dom = fw2.from_problem(prob, device="cuda:0")
+    rng = np.random.default_rng(len(shape) * 100 + L)
+    return dom, rng.standard_normal(dom.field_numel(fw2.FIELD_ALL)).astype(np.float32)
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("offset", [0, 1])          # packed buffer on 16 bytes, or 4 past them
+def test_device_fields_equal_host_fields(shape, offset):
+    import torch
+    for L, masks in ((1, (15, 1, 2, 4, 8, 6, 9)), (3, (15, 12))):
+        dom, values = _domain(shape, L)
+        for mask in masks:
+            n = dom.field_numel(mask)
+            buf = torch.zeros(n + offset, dtype=torch.float32, device="cuda:0")[offset:]
+            buf.copy_(torch.as_tensor(values[:n]))
+            dom.write_fields({k: np.zeros(s, np.float32) for k, s in dom._sizes(fw2.FIELD_ALL)})
+            dom.write_fields_device(buf, mask)
+            by_device = dom.read_fields(fw2.FIELD_ALL)
+            dom.write_fields({k: np.zeros(s, np.float32) for k, s in dom._sizes(fw2.FIELD_ALL)})
+            parts = dom.field_views(values[:n], mask)
+            dom.write_fields(parts, mask)
+            by_host = dom.read_fields(fw2.FIELD_ALL)
+            for k in by_host:
+                assert np.array_equal(by_device[k], by_host[k]), (shape, L, mask, k)
+            out = torch.full((n + offset,), -1.0, dtype=torch.float32, device="cuda:0")[offset:]
+            fw2._check(fw2.lib().fw2_read_fields(dom._h, mask, out.data_ptr(), fw2.DEVICE))
+            host = np.concatenate([by_host[k].reshape(-1) for k, _ in dom._sizes(mask)])
+            assert np.array_equal(out.cpu().numpy(), host), (shape, L, mask)
+        dom.destroy_domain()
