@@ -152,6 +152,40 @@ void make_layout(const fw2_domain_desc *d, Layout *ly)
     ly->total = end;
 }
 
+// Column tile and planes per block of the 3D sweeps.  A block marches over
+// `rows` planes after a prologue worth about two (the z window and the rings),
+// and the busiest of the 256 CUs sets the time, so the cost of a choice is
+//   ceil(blocks / CUs) * (rows + 2) * block threads,
+// raised where a CU holds few wavefronts to hide the latency of a plane.
+// Measured step times against the fixed 64 x 8 x 64 (L = 2 where not said):
+// 64^3 20.8 us against 220 (rows = 2), 256 x 256 x 64 135 against 246
+// (rows = 16), 160^3 138 against 250 (32 x 8, rows = 16), 203 x 149 x 177,
+// L = 3 264 against 327 (32 x 8, rows = 12), 300 x 200 x 100, L = 4 315
+// against 400 (rows = 8); 512^3 4.44 ms with 64, 128 or 256 planes.  The
+// 32 x 8 tile wins where it pads x less; at equal padding it is 7% slower
+// (145 against 135 us at 256 x 256 x 64), hence its factor.  More than four
+// mechanisms have the 64 x 8 tile only.
+fw2::KernelConfig sweep3d_config(const fw2::Geometry &g, int L)
+{
+    constexpr int kCUs = 256;
+    fw2::KernelConfig best{3, 64, 64};
+    double best_cost = HUGE_VAL;
+    for (int tile = 0; tile < (L <= 4 ? 2 : 1); ++tile) {
+        const int bx = tile == 0 ? 64 : 32, waves = tile == 0 ? 8 : 4;
+        const int64_t cols = (int64_t)((g.n[0] + bx - 1) / bx) * ((g.n[1] + 7) / 8);
+        for (int rows : {64, 32, 24, 16, 12, 8, 6, 4, 3, 2, 1}) {
+            const int64_t per_cu = (cols * ((g.n[2] + rows - 1) / rows) + kCUs - 1) / kCUs;
+            const double cost = (double)per_cu * (rows + 2) * waves * (tile == 0 ? 1.0 : 1.08) *
+                                (1.0 + 3.0 / (double)(per_cu * waves));
+            if (cost < best_cost) {
+                best_cost = cost;
+                best = fw2::KernelConfig{3, bx, rows, tile == 0 ? 0 : 8};
+            }
+        }
+    }
+    return best;
+}
+
 // (A, B0, B1) of the multipliers rho0 (1 + A kappa0 p), kappa0 (1 + kappa0 B p).
 void nl_coefficients(const fw2_domain_desc *d, double *A, double *B0, double *B1)
 {
@@ -654,7 +688,7 @@ fw2_status fw2_create_domain(const fw2_domain_desc *desc, void *dev_workspace, u
         a.w1[ax] = a.w2[ax] = nullptr;
     }
 
-    d->kc = nd == 2 ? fw2::KernelConfig{1, 256, 4} : fw2::KernelConfig{3, 64, 64};
+    d->kc = nd == 2 ? fw2::KernelConfig{1, 256, 4} : sweep3d_config(g, L);
     if (const char *ev = std::getenv("FW2_KERNEL_CONFIG")) {      // "variant,bx,rows[,by]" (tuning runs)
         int v = 0, bx = 0, ry = 0, by = 0;
         const int nparsed = std::sscanf(ev, "%d,%d,%d,%d", &v, &bx, &ry, &by);

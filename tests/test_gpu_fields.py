@@ -43,3 +43,31 @@ def test_device_fields_equal_host_fields(shape, offset):
             host = np.concatenate([by_host[k].reshape(-1) for k, _ in dom._sizes(mask)])
             assert np.array_equal(out.cpu().numpy(), host), (shape, L, mask)
         dom.destroy_domain()
+
+
+@pytest.mark.parametrize("n", [(64, 64, 64), (45, 30, 70), (130, 9, 40), (33, 8, 5), (96, 40, 3)])
+@pytest.mark.parametrize("L", [2, 5])
+def test_3d_tile_and_march_choice_does_not_change_results(n, L, monkeypatch):
+    """The tile and planes per block picked from the grid against one fixed
+    choice, bit for bit (the per-point arithmetic does not depend on them)."""
+    prob = W.random_medium(n, L, 3, seed=n[0] + L, nb=1, ntr=1)
+    prob.src_idx = np.array([prob.npts // 2], np.int64)
+    prob.src_sig, prob.src_w = np.zeros(1, np.int32), np.ones(1, np.float32)
+    prob.signals = np.full((1, 4), 1e4, np.float32)
+    prob.rcv_idx = np.array([0, prob.npts // 3, prob.npts - 1], np.int64)
+    state = W.random_state(3, L, n, seed=3)
+    got = []
+    for config in (None, "3,64,64"):
+        if config is None:
+            monkeypatch.delenv("FW2_KERNEL_CONFIG", raising=False)
+        else:
+            monkeypatch.setenv("FW2_KERNEL_CONFIG", config)
+        dom = fw2.from_problem(prob, device="cuda:0", cap_steps=5)
+        dom.write_fields(dict(zip(("p", "v", "psi1", "psi2"), state)))
+        dom.step(5)
+        f = dom.read_fields(fw2.FIELD_ALL)
+        got.append((f, dom.trace.cpu().numpy()))
+        dom.destroy_domain()
+    for k in got[0][0]:
+        assert np.array_equal(got[0][0][k], got[1][0][k]), k
+    assert np.array_equal(got[0][1], got[1][1])
