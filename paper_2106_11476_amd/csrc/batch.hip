@@ -59,10 +59,10 @@ __global__ void __launch_bounds__(256) batch_sparse(const BatchTable *__restrict
     if (d >= T->n) return;
     const BatchEntry &e = T->e[d];
     const long long step = *e.rcv.step;             // the entry's one counter (sources share it)
-    if (step < e.n_steps && step < e.src.n_t)
-        for (int q = threadIdx.x; q < e.src.n; q += blockDim.x) {
-            const int64_t pi = padded_index(e.src.geo, e.src.idx[q]);
-            e.src.p[pi] = e.src.p[pi] + e.src.w[q] * e.src.signals[(int64_t)e.src.sig[q] * e.src.n_t + step];
+    if (step < e.n_steps && step < e.a.src.n_t)
+        for (int q = threadIdx.x; q < e.a.src.n; q += blockDim.x) {
+            const int64_t pi = padded_index(e.a.src.geo, e.a.src.idx[q]);
+            e.a.src.p[pi] = e.a.src.p[pi] + e.a.src.w[q] * e.a.src.signals[(int64_t)e.a.src.sig[q] * e.a.src.n_t + step];
         }
     __syncthreads();
     if (step < e.n_steps && step < e.rcv.cap)

@@ -45,6 +45,7 @@ struct Layout {
     fw2::Geometry geo;
     int n_float;               // float arrays
     uint64_t float_base;       // byte offset of array 0 (x = 0 lands 256-byte aligned)
+    int64_t shadow;            // elements from the state block to its shadow, 0 without one
     uint64_t label_off;        // 0 if no label array
     uint64_t tab_off[2][3];    // [nabla-1][axis] (b, c) tables
     uint64_t w_off[2][3];      // [nabla-1][axis] w tables
@@ -113,6 +114,36 @@ fw2_status validate_scalars(const fw2_domain_desc *d)
     return FW2_OK;
 }
 
+// 2D grids advanced by one launch a step, out of place (step_f2.hip): their
+// workspace holds a second state block.  The two state blocks and the medium
+// have to stay in the 256 MiB last-level cache (the bound leaves a little over,
+// as not all of it is touched at once).  Measured, us per step, two phases
+// against one launch: 128^2, L = 2 13.6 / 5.0; 480^2, L = 2 17.1 / 8.0;
+// 1024^2, L = 3 37.7 / 31.2; 1300 x 1200, L = 4 67.2 / 49.4; 1600^2, L = 2
+// (255 MiB) 64.8 / 54.7; 2000^2, L = 1 (269 MiB) 72.8 / 74.0; past it 1700^2,
+// L = 2 (283 MiB) 70.2 / 79.3, 1400^2, L = 4 (325 MiB) 74.1 / 86.8.
+constexpr int64_t kOneLaunchBytes = (int64_t)264 << 20;
+// The most sources a one-launch step takes (every tile reads the list).
+constexpr int32_t kOneLaunchSources = 4096;
+
+bool one_launch_size(const fw2_domain_desc *d, int64_t stride)
+{
+    const int n_state = 1 + d->ndim + 2 * d->ndim * d->n_relax;
+    return d->ndim == 2 && d->n_relax <= 4 && (2 * n_state + 3) * stride * 4 <= kOneLaunchBytes;
+}
+
+// Tile rows of the one-launch step: the smallest tiles (shortest load latency)
+// while every tile has a CU of its own, then 16 rows while those do, then the
+// tile whose registers let two blocks share a CU (480^2, L = 2: 16 rows 8.0 us
+// a step, 8 rows 8.7; 600 x 500, L = 3: 12 rows 12.3, 16 rows 14.9, 8 rows
+// 14.9; 1024^2, L = 2: 16 rows 23.1, 12 rows 25.4).
+int one_launch_rows(const fw2::Geometry &g, int L)
+{
+    const int64_t cols = (g.n[0] + 63) / 64;
+    if (cols * ((g.n[1] + 7) / 8) <= 256) return 8;
+    return L <= 2 || cols * ((g.n[1] + 15) / 16) <= 256 ? 16 : 12;
+}
+
 void make_layout(const fw2_domain_desc *d, Layout *ly)
 {
     fw2::Geometry &g = ly->geo;
@@ -125,7 +156,10 @@ void make_layout(const fw2_domain_desc *d, Layout *ly)
     g.stride = g.plane * planes;                           // multiple of 64 elements
     g.origin = (d->ndim == 3 ? H * g.plane : 0) + H * g.pitch + H;
     const int L = d->n_relax;
-    ly->n_float = 1 + d->ndim + 2 * d->ndim * L + 3;
+    const int n_state = 1 + d->ndim + 2 * d->ndim * L;
+    const bool small = one_launch_size(d, g.stride);
+    ly->n_float = n_state + 3 + (small ? n_state : 0);     // state, medium, shadow of the state
+    ly->shadow = small ? (int64_t)(n_state + 3) * g.stride : 0;
     ly->float_base = kAlign + kAlign - (uint64_t)(H * 4) % kAlign;   // x = 0 on a 256-byte boundary
     uint64_t end = ly->float_base + (uint64_t)ly->n_float * g.stride * 4;
     end = align_up(end, kAlign);
@@ -186,6 +220,16 @@ fw2::KernelConfig sweep3d_config(const fw2::Geometry &g, int L)
     return best;
 }
 
+// Rows per block of the two-phase 2D sweeps: a block waits for memory once a
+// row, so grids of few tiles take fewer rows (us per step: 480^2, L = 2, 240
+// tiles of 4 rows: 17.1 with 4, 13.6 with 2, 13.2 with 1; 700 x 650, 489
+// tiles: 21.3, 19.7, 22.0; 900 x 1000, L = 3, 1000 tiles: 35.4, 38.5, 41.6).
+int sweep2d_rows(const fw2::Geometry &g)
+{
+    const int64_t tiles = (int64_t)((g.n[0] + 255) / 256) * ((g.n[1] + 3) / 4);
+    return tiles <= 256 ? 1 : (tiles <= 512 ? 2 : 4);
+}
+
 // (A, B0, B1) of the multipliers rho0 (1 + A kappa0 p), kappa0 (1 + kappa0 B p).
 void nl_coefficients(const fw2_domain_desc *d, double *A, double *B0, double *B1)
 {
@@ -231,6 +275,7 @@ struct fw2_domain {
     int *flag = nullptr;
     fw2::StepArgs args;
     fw2::KernelConfig kc;
+    fw2::KernelConfig one{0, 0, 0};  // one-launch step (variant 4), or variant 0: not used
     fw2::SparseArgs src, rcv;
     hipStream_t stream = nullptr;
     hipStream_t capture = nullptr;
@@ -257,8 +302,9 @@ namespace {
 
 // The velocity sweeps record the receivers in an extra block of their
 // launch; the one-thread-per-point kernel leaves them to a launch of their own.
-void sync_receiver_args(fw2_domain *d)
+void sync_sparse_args(fw2_domain *d)
 {
+    d->args.src = d->src;
     d->args.rcv = d->rcv;
     if (d->kc.variant == 0) d->args.rcv.step = nullptr;
 }
@@ -289,6 +335,40 @@ fw2_status enqueue_step(fw2_domain *d, TimingSlot *ts)
     return FW2_OK;
 }
 
+// Whether steps run as one launch each: decided by the grid when the domain
+// is created and by the number of sources; kernel timing takes the phases.
+bool one_launch(const fw2_domain *d) { return d->one.variant == 4 && !d->timing && d->src.n <= kOneLaunchSources; }
+
+// Step k of a run of one-launch steps from the state block at src to that at
+// dst: its sources are those k past the device counter, and it records the
+// receivers of step k - 1, whose pressure it reads.  finish_one_launch then
+// records the last step's receivers and moves the counter past the run.
+fw2_status enqueue_one_launch(fw2_domain *d, int32_t k, const float *src, float *dst, hipStream_t s)
+{
+    const int L = d->desc.n_relax, nd = d->desc.ndim;
+    const int64_t S = d->ly.geo.stride;
+    fw2::StepArgs a = d->args;
+    a.p = const_cast<float *>(src);
+    a.v = a.p + S;
+    a.psi1 = a.p + (int64_t)(1 + nd) * S;
+    a.psi2 = a.psi1 + (int64_t)nd * L * S;
+    a.out = ((int64_t)(uintptr_t)dst - (int64_t)(uintptr_t)src) / 4;   // both 4-byte aligned
+    a.src.off = k;
+    a.rcv.off = k - 1;
+    a.rcv.p = a.p;
+    FW2_HIP(fw2::launch_pressure(a, L, d->desc.relax_scheme, d->one, s));
+    return FW2_OK;
+}
+
+fw2_status finish_one_launch(fw2_domain *d, int32_t n, const float *last, hipStream_t s)
+{
+    fw2::SparseArgs rcv = d->rcv;
+    rcv.p = const_cast<float *>(last);
+    rcv.off = n - 1;
+    FW2_HIP(fw2::launch_receivers(rcv, s));
+    return FW2_OK;
+}
+
 fw2_status enqueue_step_on(fw2_domain *d, hipStream_t s)
 {
     const int L = d->desc.n_relax, sch = d->desc.relax_scheme;
@@ -299,12 +379,24 @@ fw2_status enqueue_step_on(fw2_domain *d, hipStream_t s)
     return FW2_OK;
 }
 
+// n steps.  One-launch steps go in pairs, to the shadow block and back, so
+// that the state always ends where the domain's fields are.
+fw2_status enqueue_steps_on(fw2_domain *d, int32_t n, hipStream_t s)
+{
+    const int32_t m = one_launch(d) ? n & ~1 : 0;
+    float *const st[2] = {d->args.p, d->args.p + d->ly.shadow};
+    fw2_status r = FW2_OK;
+    for (int32_t k = 0; k < m && r == FW2_OK; ++k) r = enqueue_one_launch(d, k, st[k & 1], st[1 - (k & 1)], s);
+    if (m > 0 && r == FW2_OK) r = finish_one_launch(d, m, st[0], s);
+    for (int32_t k = m; k < n && r == FW2_OK; ++k) r = enqueue_step_on(d, s);
+    return r;
+}
+
 fw2_status build_graph(fw2_domain *d)
 {
     if (!d->capture) FW2_HIP(hipStreamCreateWithFlags(&d->capture, hipStreamNonBlocking));
     FW2_HIP(hipStreamBeginCapture(d->capture, hipStreamCaptureModeThreadLocal));
-    fw2_status st = FW2_OK;
-    for (int k = 0; k < d->graph_chunk && st == FW2_OK; ++k) st = enqueue_step_on(d, d->capture);
+    fw2_status st = enqueue_steps_on(d, d->graph_chunk, d->capture);
     hipGraph_t graph = nullptr;
     hipError_t e = hipStreamEndCapture(d->capture, &graph);
     if (st != FW2_OK) {
@@ -688,17 +780,21 @@ fw2_status fw2_create_domain(const fw2_domain_desc *desc, void *dev_workspace, u
         a.w1[ax] = a.w2[ax] = nullptr;
     }
 
-    d->kc = nd == 2 ? fw2::KernelConfig{1, 256, 4} : sweep3d_config(g, L);
+    d->kc = nd == 2 ? fw2::KernelConfig{1, 256, sweep2d_rows(g)} : sweep3d_config(g, L);
+    if (ly.shadow) d->one = fw2::KernelConfig{4, 64, one_launch_rows(g, L)};
     if (const char *ev = std::getenv("FW2_KERNEL_CONFIG")) {      // "variant,bx,rows[,by]" (tuning runs)
         int v = 0, bx = 0, ry = 0, by = 0;
         const int nparsed = std::sscanf(ev, "%d,%d,%d,%d", &v, &bx, &ry, &by);
         const bool parsed = nparsed == 3 || nparsed == 4;
         const bool ok2 = nd == 2 && by == 0 && (v == 0 || v == 1 || v == 2) && (bx == 64 || bx == 128 || bx == 256);
+        if (parsed && v == 4 && by == 0 && ly.shadow && (ry == 8 || ry == 12 || ry == 16)) d->one = fw2::KernelConfig{4, bx, ry};
         const bool tile3 = by == 0 ? (bx == 16 || bx == 32 || bx == 64)
                                    : (v == 3 && ((bx == 64 && by == 4) || (bx == 32 && by == 8)));
         const bool ok3 = nd == 3 && (v == 0 || ((v >= 1 && v <= 3) && tile3));
-        if (parsed && (ok2 || ok3) && ry >= 1 && ry <= 1024)
+        if (parsed && (ok2 || ok3) && ry >= 1 && ry <= 1024) {
             d->kc = fw2::KernelConfig{v, bx, ry, by};
+            d->one.variant = 0;
+        }
     }
 
     std::memset(&d->src, 0, sizeof(d->src));
@@ -706,7 +802,7 @@ fw2_status fw2_create_domain(const fw2_domain_desc *desc, void *dev_workspace, u
     d->src.geo = d->rcv.geo = g;
     d->src.p = d->rcv.p = a.p;
     d->src.step = d->rcv.step = d->counter;
-    sync_receiver_args(d);
+    sync_sparse_args(d);
     FW2_HIP_C(hipStreamSynchronize(d->stream));
 #undef FW2_HIP_C
     *out = d;
@@ -741,6 +837,7 @@ fw2_status fw2_add_source(fw2_domain *d, int32_t n_pts, const int64_t *flat_idx,
     d->src.w = weight;
     d->src.signals = signals;
     d->src.n_t = n_t;
+    sync_sparse_args(d);
     return FW2_OK;
 }
 
@@ -761,7 +858,7 @@ fw2_status fw2_add_receivers(fw2_domain *d, int32_t n_rcv, const int64_t *flat_i
     d->rcv.idx = flat_idx;
     d->rcv.trace = trace;
     d->rcv.cap = n_rcv > 0 ? cap_steps : 0;
-    sync_receiver_args(d);
+    sync_sparse_args(d);
     return FW2_OK;
 }
 
@@ -796,11 +893,9 @@ fw2_status fw2_step(fw2_domain *d, int32_t n)
             d->step += d->graph_chunk;
         }
     }
-    for (; left > 0; --left) {
-        fw2_status st = enqueue_step(d, nullptr);
-        if (st != FW2_OK) return st;
-        d->step++;
-    }
+    fw2_status st = enqueue_steps_on(d, left, d->stream);
+    if (st != FW2_OK) return st;
+    d->step += left;
     return FW2_OK;
 }
 
@@ -946,6 +1041,12 @@ fw2_status enqueue_step_into(fw2_domain *d, const float *src, float *dst, hipStr
 fw2_status enqueue_steps_into(fw2_domain *d, int32_t n, const float *first, float *states, hipStream_t s)
 {
     const int64_t B = state_floats(d);
+    if (one_launch(d)) {
+        fw2_status st = FW2_OK;
+        for (int32_t i = 0; i < n && st == FW2_OK; ++i)
+            st = enqueue_one_launch(d, i, i == 0 ? first : states + (int64_t)(i - 1) * B, states + (int64_t)i * B, s);
+        return st == FW2_OK ? finish_one_launch(d, n, states + (int64_t)(n - 1) * B, s) : st;
+    }
     for (int32_t i = 0; i < n; ++i) {
         fw2_status st = enqueue_step_into(d, i == 0 ? first : states + (int64_t)(i - 1) * B, states + (int64_t)i * B, s);
         if (st != FW2_OK) return st;
@@ -1334,7 +1435,6 @@ fw2_status fw2_batch_set_domains(fw2_batch *b, int32_t n, fw2_domain *const *dom
             if (fw2::batch_class(d->desc.n_relax, d->args.local_stencil) != c) continue;
             fw2::BatchEntry &e = T.e[m++];
             e.a = d->args;
-            e.src = d->src;
             e.rcv = d->rcv;
             e.n_steps = n_steps[k];
             e.L = d->desc.n_relax;

@@ -53,6 +53,7 @@ __global__ void check_kernel(const float *p, const Geometry g, float limit, int 
 
 hipError_t launch_pressure(const StepArgs &a, int L, int scheme, const KernelConfig &kc, hipStream_t st)
 {
+    if (kc.variant == 4) return launch_fused_2d(a, L, scheme, kc, st);
     return a.geo.ndim == 2 ? launch_pressure_2d(a, L, scheme, kc, st) : launch_pressure_3d(a, L, scheme, kc, st);
 }
 

@@ -43,6 +43,7 @@ struct SparseArgs {
     float *trace;            // receivers: [cap][n]
     int32_t n;               // points
     int32_t n_t;             // sources: samples per signal
+    int32_t off;             // this launch's step past the device counter
     long long cap;           // receivers: trace rows
 };
 
@@ -86,8 +87,9 @@ struct StepArgs {
     // of the velocity sweep launch, which reads p without writing it and runs
     // after the sources; rcv.step == nullptr: a separate launch does it.
     SparseArgs rcv;
+    // Sources, for the kernels that add them in the pressure phase themselves.
+    SparseArgs src;
 };
-
 
 // Kernel variant and tile shape.  variant 0: one thread per point over a
 // (64 x 8) tile, every stencil tap a cached global load (any ndim).
@@ -99,6 +101,8 @@ struct StepArgs {
 // variant 2 (3D): the same with every load of the next plane issued during
 // the current one; variant 3 (3D): only the staged planes and the z window
 // one plane ahead, the point's own values at the top of their plane.
+// variant 4 (2D, at most four mechanisms): a whole step out of place in one
+// launch of 64 x `rows` tiles (step_f2.hip), passed to launch_pressure.
 struct KernelConfig {
     int variant;
     int bx;
@@ -115,7 +119,7 @@ constexpr int kMaxBatch = 64;
 
 struct BatchEntry {
     StepArgs a;
-    SparseArgs src, rcv;
+    SparseArgs rcv;          // (the sources are a.src)
     long long n_steps;
     int32_t L, scheme;
     int32_t tile_base, tiles;        // tiles of bx columns x rows
@@ -173,6 +177,8 @@ hipError_t launch_pressure_2d(const StepArgs &a, int L, int scheme, const Kernel
 hipError_t launch_velocity_2d(const StepArgs &a, int L, int scheme, const KernelConfig &kc, hipStream_t stream);
 hipError_t launch_pressure_3d(const StepArgs &a, int L, int scheme, const KernelConfig &kc, hipStream_t stream);
 hipError_t launch_velocity_3d(const StepArgs &a, int L, int scheme, const KernelConfig &kc, hipStream_t stream);
+
+hipError_t launch_fused_2d(const StepArgs &a, int L, int scheme, const KernelConfig &kc, hipStream_t stream);
 
 // Launchers (kernels.hip).  All enqueue on `stream` and return the launch error.
 hipError_t launch_pressure(const StepArgs &a, int L, int scheme, const KernelConfig &kc, hipStream_t stream);

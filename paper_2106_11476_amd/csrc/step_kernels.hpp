@@ -205,10 +205,14 @@ __global__ void __launch_bounds__(kBX * kBY) velocity_kernel(const StepArgs a)
 // takes a contiguous band of tiles, keeping halo lines in one L2.
 // ---------------------------------------------------------------------------
 
+// A bijection of [0, nblocks) for any nblocks: the first nblocks % 8 XCDs
+// take one tile more.  (Grids whose tile count was no multiple of 8 kept the
+// plain order before and fetched their halo lines once per XCD: a 900 x 1000
+// grid of 945 tiles took 38.7 us a step where 1024 x 1024 took 34.0.)
 __device__ __forceinline__ int tile_of_block(int bid, int nblocks)
 {
-    if (nblocks % 8 != 0) return bid;
-    return (bid % 8) * (nblocks / 8) + bid / 8;
+    const int x = bid % 8, rem = nblocks % 8;
+    return x * (nblocks / 8) + min(x, rem) + bid / 8;
 }
 
 // Pointers into device global memory (address space 1), so that the
@@ -566,12 +570,12 @@ __device__ __forceinline__ int64_t padded_index(const Geometry &g, int64_t f)
     return g.origin + z * g.plane + y * g.pitch + x;
 }
 
-// The receivers of the current step, recorded by one whole block, then the
-// device step counter advanced (one block, so no other block reads the
-// counter meanwhile).
+// The receivers of the launch's step, recorded by one whole block, then the
+// device step counter advanced past it (one block, so no other block reads
+// the counter meanwhile).
 __device__ __forceinline__ void record_receivers(const SparseArgs &s)
 {
-    const long long step = *s.step;
+    const long long step = *s.step + s.off;
     if (step < s.cap)
         for (int r = threadIdx.x; r < s.n; r += blockDim.x)
             s.trace[step * s.n + r] = s.p[padded_index(s.geo, s.idx[r])];
