@@ -25,11 +25,12 @@
 //       lam_D_a = w2 lam_S + sum c2 lam_psi2 (new)
 //   A3  v points inside the grid: lam_v_a -= D^+(lam_D_a)
 // using (D^-)^T = -(D^+) and (D^+)^T = -(D^-).
-// The phases run as one-thread-per-point kernels, two per step: A3 of a step
-// is deferred into the velocity kernel (A1) of the next call, A_rcv runs in
-// extra blocks of that kernel, and A0 of the step before is fused into the
-// pressure kernel (A2) when its state is at hand, writing that step's p''
-// into the second p'' buffer (this step's is still read by neighbours).
+// The phases run as two kernels per step (from LDS tiles in 2D, one thread per
+// point in 3D): A3 of a step is deferred into the velocity kernel (A1) of the
+// next call, A_rcv runs in extra blocks of that kernel, and A0 of the step
+// before is fused into the pressure kernel (A2) when its state is at hand,
+// writing that step's p'' into the second p'' buffer (this step's is still
+// read by neighbours).
 #include "kernels.hpp"
 
 #include <cstdio>
@@ -76,6 +77,8 @@ struct AdjArgs {
     const int64_t *rcv_idx;  // receivers (flat indices), added into lam_p by the
     const float *residual;   // velocity kernel's extra blocks: trace - obs of this step
     int n_rcv;               // 0: no receiver blocks
+    SparseArgs src;          // sources of the step before, added to pq by the tile
+    long long src_step;      // kernel (n = 0: none, or a launch of their own)
 };
 
 // Point block of a 1D launch.  Blocks are dealt to the 8 XCDs round-robin
@@ -204,14 +207,11 @@ __global__ void __launch_bounds__(kABX *kABY) adj_velocity(const AdjArgs A)
     const float *m1 = A.sp + (int64_t)(1 + nd) * st;
     float *lv = A.lp + st;
     float *lm1 = A.lp + (int64_t)(1 + nd) * st;
+    float nv[nd], nDv[nd], nqr[nd], nm[nd][L];               // results, stored last
 #pragma unroll
     for (int a = 0; a < nd; ++a) {
-        float *oDv = A.lDv + a * st, *oqr = A.lqr + a * st;
-        if (c3[a] == g.n[a] - 1) {                       // outside the grid: no adjoint flow
-            oDv[idx] = 0.0f;
-            oqr[idx] = 0.0f;
-            continue;
-        }
+        nDv[a] = nqr[a] = 0.0f;
+        if (c3[a] == g.n[a] - 1) continue;                   // outside the grid: no adjoint flow
         const int64_t o = aoff(g, a);
         const float D = dplus(A.pp, g, A.f.g, A.f.g11, a, nd, idx);
         const int t = slot_v(c3[a], g.n[a], A.f.nb[a]) * A.f.n_labels + lab;
@@ -225,23 +225,29 @@ __global__ void __launch_bounds__(kABX *kABY) adj_velocity(const AdjArgs A)
         const float kap_a = 0.5f * (A.f.kap[idx] + A.f.kap[idx + o]);
         const float Q = rho_a * (1.0f + (A.f.nlA * kap_a) * pbar);
         float lva = lv[a * st + idx];
-        if (DEFER_A3) {
-            lva -= dplus(A.lDp + a * st, g, A.f.g, A.f.g11, a, nd, idx);
-            lv[a * st + idx] = lva;
-        }
+        if (DEFER_A3) lva -= dplus(A.lDp + a * st, g, A.f.g, A.f.g11, a, nd, idx);
+        nv[a] = lva;
         const float lS = -A.f.dt * lva / Q;
         const float lQ = A.f.dt * Sv * lva / (Q * Q);
         float lD = w * lS;
 #pragma unroll
         for (int nu = 0; nu < L; ++nu) {
-            const int64_t c = (int64_t)(a * L + nu) * st + idx;
             const float2 q = bc[nu];
-            const float lmn = ntld(&lm1[c]);
+            const float lmn = ntld(&lm1[(int64_t)(a * L + nu) * st + idx]);
             lD = fmaf(q.y, lmn, lD);
-            ntst(&lm1[c], fmaf(q.x, lmn, lS));
+            nm[a][nu] = fmaf(q.x, lmn, lS);
         }
-        oDv[idx] = lD;
-        oqr[idx] = (lQ * rho_a) * A.f.nlA;      // the multiplier's coefficient A folded in
+        nDv[a] = lD;
+        nqr[a] = (lQ * rho_a) * A.f.nlA;        // the multiplier's coefficient A folded in
+    }
+#pragma unroll
+    for (int a = 0; a < nd; ++a) {
+        A.lDv[a * st + idx] = nDv[a];
+        A.lqr[a * st + idx] = nqr[a];
+        if (c3[a] == g.n[a] - 1) continue;
+        if (DEFER_A3) lv[a * st + idx] = nv[a];
+#pragma unroll
+        for (int nu = 0; nu < L; ++nu) ntst(&lm1[(int64_t)(a * L + nu) * st + idx], nm[a][nu]);
     }
 }
 
@@ -278,9 +284,9 @@ __global__ void __launch_bounds__(kABX *kABY) adj_pressure(const AdjArgs A)
     const float S = A.sS[idx];
     const float lS = -A.f.dt * lpp / K;
     const float lK = A.f.dt * S * lpp / (K * K);
-    A.lp[idx] = lpp + lK * x * q;
-    A.gk[idx] = gk + lK * (1.0f + 2.0f * q * p0);
+    const float nlp = lpp + lK * x * q, ngk = gk + lK * (1.0f + 2.0f * q * p0);
     float *lm2 = A.lp + (int64_t)(1 + nd + nd * L) * st;
+    float nD[nd], nm[nd][L];                                 // results, stored last
 #pragma unroll
     for (int a = 0; a < nd; ++a) {
         const int t = slot_p(c3[a], g.n[a], A.f.nb[a]) * A.f.n_labels + lab;
@@ -288,14 +294,14 @@ __global__ void __launch_bounds__(kABX *kABY) adj_pressure(const AdjArgs A)
         float lD = A.f.w2[a][t] * lS;
 #pragma unroll
         for (int nu = 0; nu < L; ++nu) {
-            const int64_t c = (int64_t)(a * L + nu) * st + idx;
             const float2 qq = bc[nu];
-            const float lmn = ntld(&lm2[c]);
+            const float lmn = ntld(&lm2[(int64_t)(a * L + nu) * st + idx]);
             lD = fmaf(qq.y, lmn, lD);
-            ntst(&lm2[c], fmaf(qq.x, lmn, lS));
+            nm[a][nu] = fmaf(qq.x, lmn, lS);
         }
-        A.lDp[a * st + idx] = lD;
+        nD[a] = lD;
     }
+    float npq = 0.0f, nS = 0.0f;
     if (WITH_A0) {
         const float *vq = A.sq + st;
         const float *m2q = A.sq + (int64_t)(1 + nd + nd * L) * st;
@@ -311,7 +317,301 @@ __global__ void __launch_bounds__(kABX *kABY) adj_pressure(const AdjArgs A)
         }
         const float q0 = A.sq[idx];
         const float K0 = x * (1.0f + q * q0);
-        A.pq[idx] = q0 - A.f.dt * S0 / K0;
+        npq = q0 - A.f.dt * S0 / K0;
+        nS = S0;
+    }
+    A.lp[idx] = nlp;
+    A.gk[idx] = ngk;
+#pragma unroll
+    for (int a = 0; a < nd; ++a) {
+        A.lDp[a * st + idx] = nD[a];
+#pragma unroll
+        for (int nu = 0; nu < L; ++nu) ntst(&lm2[(int64_t)(a * L + nu) * st + idx], nm[a][nu]);
+    }
+    if (WITH_A0) {
+        A.pq[idx] = npq;
+        A.sS[idx] = nS;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// 2D reverse step from LDS tiles of 64 columns x TY rows, one thread a point.
+// One thread a point with every stencil tap a load of its own (45 and 53
+// vector loads, half of them off a 64-byte boundary and so two accesses per
+// 16 lanes) keeps the L1 pipeline busy three quarters of the time while HBM
+// is not: 66 and 72 us for 107 and 135 B a point at 1536^2, L = 2.  Here a
+// block loads the fields whose neighbours it reads once, halo included, with
+// its own values, and takes the taps from LDS; the arithmetic is the same,
+// point for point.  us per reverse step, per-point against tiles (with the
+// sources added by the tile): 384^2, L = 2 19.5 / 14.6; 1024^2 65.9 / 48.9;
+// 1536^2 141 / 105.5 (5.5 TB/s of its 246 B a point, the streaming rate);
+// 1536^2, L = 4 198 / 164, L = 8 304 / 292.  Tiles of 8 rows at L <= 2, of 16
+// above: 1536^2, L = 2 105.5 / 107.3, L = 8 303 / 292.
+// ---------------------------------------------------------------------------
+
+// The most sources the tiles add themselves (each reads the list).
+constexpr int kTileSources = 4096;
+constexpr int kTX = 64;
+
+// (W x H) window of a 2D array with corner (xs, ys), loaded into registers and
+// stored to LDS; cells outside the grid are zero (the array's halo corner).
+template <int W, int H, int NT>
+struct Window {
+    static constexpr int N = (W * H + NT - 1) / NT;
+    float r[N];
+    __device__ __forceinline__ void load(const float *f, const Geometry &g, int xs, int ys, int tid)
+    {
+        const float *corner = f + (g.origin - g.pitch - 1);
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+            const int e = tid + q * NT, row = e / W, x = xs + e - row * W, y = ys + row;
+            const bool in = (unsigned)x < (unsigned)g.n[0] && (unsigned)y < (unsigned)g.n[1];
+            const uint32_t o = in ? (uint32_t)((y + 1) * (int)g.pitch + x + 1) : 0u;
+            if (e < W * H) r[q] = corner[o];
+        }
+    }
+    __device__ __forceinline__ void store(float *dst, int tid) const
+    {
+#pragma unroll
+        for (int q = 0; q < N; ++q)
+            if (tid + q * NT < W * H) dst[tid + q * NT] = r[q];
+    }
+};
+
+// D^- and D^+ from LDS: o and o2 are the strides along the axis and across it.
+__device__ __forceinline__ float tile_dminus(const float *f, const float *gw, float g11, int o, int o2)
+{
+    float D = gw[0] * (f[0] - f[-o]);
+    D = fmaf(gw[1], f[o] - f[-2 * o], D);
+    D = fmaf(gw[2], f[2 * o] - f[-3 * o], D);
+    D = fmaf(gw[3], f[3 * o] - f[-4 * o], D);
+    float cr = 0.0f;
+    cr += (f[o2] - f[o2 - o]) + (f[-o2] - f[-o - o2]);
+    return fmaf(g11, cr, D);
+}
+
+__device__ __forceinline__ float tile_dplus(const float *f, const float *gw, float g11, int o, int o2)
+{
+    float D = gw[0] * (f[o] - f[0]);
+    D = fmaf(gw[1], f[2 * o] - f[-o], D);
+    D = fmaf(gw[2], f[3 * o] - f[-2 * o], D);
+    D = fmaf(gw[3], f[4 * o] - f[-3 * o], D);
+    float cr = 0.0f;
+    cr += (f[o + o2] - f[o2]) + (f[o - o2] - f[-o2]);
+    return fmaf(g11, cr, D);
+}
+
+#define ADJ_TILE                                                                    \
+    constexpr int NT = kTX * TY;                                                    \
+    const Geometry &g = A.f.geo;                                                    \
+    const int blk = xcd_block(blockIdx.x, A.nblocks);                               \
+    const int x0 = (blk % A.nbx) * kTX, y0 = (blk / A.nbx) * TY;                    \
+    const int tid = threadIdx.x, tx = tid % kTX, ty = tid / kTX;                    \
+    const int i = x0 + tx, j = y0 + ty;                                             \
+    const bool live = i < g.n[0] && j < g.n[1];                                     \
+    const int64_t st = g.stride;                                                    \
+    const int64_t idx = g.origin + (int64_t)j * g.pitch + i;
+
+// A1 with the deferred A3 (adj_velocity) from tiles.
+template <int L, int TY>
+__global__ void __launch_bounds__(kTX *TY) adj_velocity_tile(const AdjArgs A)
+{
+    if ((int)blockIdx.x >= A.nblocks) {
+        const int q = ((int)blockIdx.x - A.nblocks) * (kTX * TY) + (int)threadIdx.x;
+        if (q < A.n_rcv) atomicAdd(&A.lp[pidx(A.f.geo, A.rcv_idx[q])], A.residual[q]);
+        return;
+    }
+    ADJ_TILE
+    // p'' and lam_D with the reach of D^+: 3 cells before, 4 after, 1 across
+    constexpr int PW = kTX + 7, PH = TY + 7, XH = TY + 2, YW = kTX + 2;
+    __shared__ float sp[PW * PH], sx[PW * XH], sy[YW * PH];
+    Window<PW, PH, NT> wp;
+    Window<PW, XH, NT> wx;
+    Window<YW, PH, NT> wy;
+    wp.load(A.pp, g, x0 - 3, y0 - 3, tid);
+    wx.load(A.lDp, g, x0 - 3, y0 - 1, tid);
+    wy.load(A.lDp + st, g, x0 - 1, y0 - 3, tid);
+    const float *m1 = A.sp + (int64_t)3 * st;
+    float *lv = A.lp + st;
+    float *lm1 = A.lp + (int64_t)3 * st;
+    int lab = 0;
+    float r0 = 1.0f, k0 = 1.0f, rn[2] = {1.0f, 1.0f}, kn[2] = {1.0f, 1.0f}, lva[2] = {0.0f, 0.0f}, m[2][L], lm[2][L];
+    if (live) {
+        lab = A.f.label ? (int)A.f.label[idx] : 0;
+        r0 = A.f.rho[idx];
+        k0 = A.f.kap[idx];
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            rn[a] = A.f.rho[idx + aoff(g, a)];
+            kn[a] = A.f.kap[idx + aoff(g, a)];
+            lva[a] = lv[a * st + idx];
+#pragma unroll
+            for (int nu = 0; nu < L; ++nu) {
+                m[a][nu] = ntld(&m1[(int64_t)(a * L + nu) * st + idx]);
+                lm[a][nu] = ntld(&lm1[(int64_t)(a * L + nu) * st + idx]);
+            }
+        }
+    }
+    wp.store(sp, tid);
+    wx.store(sx, tid);
+    wy.store(sy, tid);
+    __syncthreads();
+    if (!live) return;
+    const float *P = &sp[(ty + 3) * PW + tx + 3];
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+        float *oDv = A.lDv + a * st, *oqr = A.lqr + a * st;
+        if ((a == 0 ? i : j) == g.n[a] - 1) {                // outside the grid: no adjoint flow
+            oDv[idx] = 0.0f;
+            oqr[idx] = 0.0f;
+            continue;
+        }
+        const float D = tile_dplus(P, A.f.g, A.f.g11, a == 0 ? 1 : PW, a == 0 ? PW : 1);
+        const int t = slot_v(a == 0 ? i : j, g.n[a], A.f.nb[a]) * A.f.n_labels + lab;
+        const float2 *__restrict__ bc = A.f.bc1[a] + (int64_t)t * L;
+        const float w = A.f.w1[a][t];
+        float Sv = w * D;
+#pragma unroll
+        for (int nu = 0; nu < L; ++nu) Sv += m[a][nu];
+        const float pbar = 0.5f * (P[0] + P[a == 0 ? 1 : PW]);
+        const float rho_a = 0.5f * (r0 + rn[a]);
+        const float kap_a = 0.5f * (k0 + kn[a]);
+        const float Q = rho_a * (1.0f + (A.f.nlA * kap_a) * pbar);
+        float l = lva[a];
+        l -= a == 0 ? tile_dplus(&sx[(ty + 1) * PW + tx + 3], A.f.g, A.f.g11, 1, PW)
+                    : tile_dplus(&sy[(ty + 3) * YW + tx + 1], A.f.g, A.f.g11, YW, 1);
+        const float lS = -A.f.dt * l / Q;
+        const float lQ = A.f.dt * Sv * l / (Q * Q);
+        float lD = w * lS;
+#pragma unroll
+        for (int nu = 0; nu < L; ++nu) {
+            const float2 q = bc[nu];
+            lD = fmaf(q.y, lm[a][nu], lD);
+            lm[a][nu] = fmaf(q.x, lm[a][nu], lS);
+        }
+        lv[a * st + idx] = l;
+#pragma unroll
+        for (int nu = 0; nu < L; ++nu) ntst(&lm1[(int64_t)(a * L + nu) * st + idx], lm[a][nu]);
+        oDv[idx] = lD;
+        oqr[idx] = (lQ * rho_a) * A.f.nlA;      // the multiplier's coefficient A folded in
+    }
+}
+
+// A2 and, WITH_A0, A0 of the step before (adj_pressure) from tiles.
+template <int L, bool WITH_A0, int TY>
+__global__ void __launch_bounds__(kTX *TY) adj_pressure_tile(const AdjArgs A)
+{
+    ADJ_TILE
+    // lam_D^+ and v with the reach of D^-: 4 cells before, 3 after, 1 across;
+    // p'' and kappa0 with one cell around
+    constexpr int XW = kTX + 7, XH = TY + 2, YW = kTX + 2, YH = TY + 7;
+    __shared__ float sx[XW * XH], sy[YW * YH], sp[YW * XH], sk[YW * XH];
+    __shared__ float qx[WITH_A0 ? XW * XH : 1], qy[WITH_A0 ? YW * YH : 1];
+    const float *vq = A.sq + st;
+    Window<XW, XH, NT> wx, ux;
+    Window<YW, YH, NT> wy, uy;
+    Window<YW, XH, NT> wp, wk;
+    wx.load(A.lDv, g, x0 - 4, y0 - 1, tid);
+    wy.load(A.lDv + st, g, x0 - 1, y0 - 4, tid);
+    wp.load(A.pp, g, x0 - 1, y0 - 1, tid);
+    wk.load(A.f.kap, g, x0 - 1, y0 - 1, tid);
+    if (WITH_A0) {
+        ux.load(vq, g, x0 - 4, y0 - 1, tid);
+        uy.load(vq + st, g, x0 - 1, y0 - 4, tid);
+    }
+    float *lm2 = A.lp + (int64_t)(3 + 2 * L) * st;
+    const float *m2q = A.sq + (int64_t)(3 + 2 * L) * st;
+    int lab = 0;
+    float lpp = 0.0f, gk = 0.0f, p0 = 0.0f, q = 0.0f, S = 0.0f, q1[2], q0[2], lm[2][L], mq[2][L], pq0 = 0.0f;
+    if (live) {
+        lab = A.f.label ? (int)A.f.label[idx] : 0;
+        lpp = A.lp[idx];
+        gk = A.gk[idx];
+        p0 = A.sp[idx];
+        q = A.f.nlq[idx];
+        S = A.sS[idx];
+        if (WITH_A0) pq0 = A.sq[idx];
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            q1[a] = A.lqr[a * st + idx];
+            q0[a] = A.lqr[a * st + idx - aoff(g, a)];
+#pragma unroll
+            for (int nu = 0; nu < L; ++nu) {
+                lm[a][nu] = ntld(&lm2[(int64_t)(a * L + nu) * st + idx]);
+                if (WITH_A0) mq[a][nu] = ntld(&m2q[(int64_t)(a * L + nu) * st + idx]);
+            }
+        }
+    }
+    __shared__ int ssrc[WITH_A0 ? NT : 1];
+    if (WITH_A0 && A.src.n > 0) {                    // the sources of the tile's cells
+        ssrc[tid] = 0;
+        __syncthreads();
+        for (int k = tid; k < A.src.n; k += NT) {
+            const uint32_t f = (uint32_t)A.src.idx[k], y = f / (uint32_t)g.n[0], x = f - y * (uint32_t)g.n[0];
+            if (x - (uint32_t)x0 < (uint32_t)kTX && y - (uint32_t)y0 < (uint32_t)TY)
+                ssrc[(y - (uint32_t)y0) * kTX + (x - (uint32_t)x0)] = k + 1;
+        }
+    }
+    wx.store(sx, tid);
+    wy.store(sy, tid);
+    wp.store(sp, tid);
+    wk.store(sk, tid);
+    if (WITH_A0) {
+        ux.store(qx, tid);
+        uy.store(qy, tid);
+    }
+    __syncthreads();
+    if (!live) return;
+    const float *P = &sp[(ty + 1) * YW + tx + 1], *K1 = &sk[(ty + 1) * YW + tx + 1];
+    const float *X = &sx[(ty + 1) * XW + tx + 4], *Y = &sy[(ty + 4) * YW + tx + 1];
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+        const int o = a == 0 ? 1 : YW;
+        lpp -= a == 0 ? tile_dminus(X, A.f.g, A.f.g11, 1, XW) : tile_dminus(Y, A.f.g, A.f.g11, YW, 1);
+        const float k1 = 0.5f * (K1[0] + K1[o]);
+        const float k0 = 0.5f * (K1[-o] + K1[0]);
+        const float b1 = 0.5f * (P[0] + P[o]);
+        const float b0 = 0.5f * (P[-o] + P[0]);
+        lpp += 0.5f * (q1[a] * k1 + q0[a] * k0);
+        gk += 0.5f * (q1[a] * b1 + q0[a] * b0);
+    }
+    const float x = K1[0];
+    const float K = x * (1.0f + q * p0);
+    const float lS = -A.f.dt * lpp / K;
+    const float lK = A.f.dt * S * lpp / (K * K);
+    A.lp[idx] = lpp + lK * x * q;
+    A.gk[idx] = gk + lK * (1.0f + 2.0f * q * p0);
+    float S0 = 0.0f;
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+        const int t = slot_p(a == 0 ? i : j, g.n[a], A.f.nb[a]) * A.f.n_labels + lab;
+        const float2 *__restrict__ bc = A.f.bc2[a] + (int64_t)t * L;
+        const float w = A.f.w2[a][t];
+        float lD = w * lS;
+#pragma unroll
+        for (int nu = 0; nu < L; ++nu) {
+            const float2 qq = bc[nu];
+            lD = fmaf(qq.y, lm[a][nu], lD);
+            ntst(&lm2[(int64_t)(a * L + nu) * st + idx], fmaf(qq.x, lm[a][nu], lS));
+        }
+        A.lDp[a * st + idx] = lD;
+        if (WITH_A0) {
+            const float D = a == 0 ? tile_dminus(&qx[(ty + 1) * XW + tx + 4], A.f.g, A.f.g11, 1, XW)
+                                   : tile_dminus(&qy[(ty + 4) * YW + tx + 1], A.f.g, A.f.g11, YW, 1);
+            float Sa = w * D;
+#pragma unroll
+            for (int nu = 0; nu < L; ++nu) Sa += mq[a][nu];
+            S0 += Sa;
+        }
+    }
+    if (WITH_A0) {
+        const float K0 = x * (1.0f + q * pq0);
+        float pn = pq0 - A.f.dt * S0 / K0;
+        if (A.src.n > 0 && ssrc[tid]) {
+            const int k = ssrc[tid] - 1;
+            pn = fmaf(A.src.w[k], A.src.signals[(int64_t)A.src.sig[k] * A.src.n_t + A.src_step], pn);
+        }
+        A.pq[idx] = pn;
         A.sS[idx] = S0;
     }
 }
@@ -335,11 +635,11 @@ unsigned point_grid(AdjArgs &A, dim3 block)
     return (unsigned)A.nblocks;
 }
 
-// One thread per point.  A3 of each step is deferred into the velocity
-// kernel of the next call; A0 of the step before is fused into the pressure
-// kernel when its state is given, else run at the start of the next call.
+// A3 of each step is deferred into the velocity kernel of the next call; A0 of
+// the step before is fused into the pressure kernel when its state is given,
+// else run at the start of the next call.
 template <int ND, int L>
-hipError_t adjoint_step_points(const StepArgs &f, const SparseArgs &src, const SparseArgs &rcv, const float *state,
+hipError_t adjoint_step(const StepArgs &f, const SparseArgs &src, const SparseArgs &rcv, const float *state,
                                const float *state_prev, const AdjointBuffers &b, long long step, bool have_pp,
                                const float *residual, hipStream_t st, bool *pp_next)
 {
@@ -367,16 +667,36 @@ hipError_t adjoint_step_points(const StepArgs &f, const SparseArgs &src, const S
         if (src.n > 0 && step < src.n_t)
             hipLaunchKernelGGL(adj_sources, dim3((src.n + 255) / 256), dim3(256), 0, st, b.pp, src, step);
     }
-    hipLaunchKernelGGL((adj_velocity<ND, L, true>), vgrid, block, 0, st, A);
-    if (state_prev && step >= 1) {
-        hipLaunchKernelGGL((adj_pressure<ND, L, true>), grid, block, 0, st, A);
-        if (src.n > 0 && step - 1 < src.n_t)
+    const bool with_a0 = state_prev && step >= 1;
+    const bool sources = with_a0 && src.n > 0 && step - 1 < src.n_t;
+    if constexpr (ND == 2) {
+        constexpr int TY = L <= 2 ? 8 : 16;
+        A.nbx = (f.geo.n[0] + kTX - 1) / kTX;
+        A.nby = (f.geo.n[1] + TY - 1) / TY;
+        A.nblocks = A.nbx * A.nby;
+        const dim3 tile(kTX * TY);
+        const int rcv_blocks = (A.n_rcv + kTX * TY - 1) / (kTX * TY);
+        const bool in_tiles = sources && src.n <= kTileSources;
+        A.src = src;
+        if (!in_tiles) A.src.n = 0;
+        A.src_step = step - 1;
+        hipLaunchKernelGGL((adj_velocity_tile<L, TY>), dim3(A.nblocks + rcv_blocks), tile, 0, st, A);
+        if (with_a0)
+            hipLaunchKernelGGL((adj_pressure_tile<L, true, TY>), dim3(A.nblocks), tile, 0, st, A);
+        else
+            hipLaunchKernelGGL((adj_pressure_tile<L, false, TY>), dim3(A.nblocks), tile, 0, st, A);
+        if (sources && !in_tiles)
             hipLaunchKernelGGL(adj_sources, dim3((src.n + 255) / 256), dim3(256), 0, st, b.pq, src, step - 1);
-        *pp_next = true;
     } else {
-        hipLaunchKernelGGL((adj_pressure<ND, L, false>), grid, block, 0, st, A);
-        *pp_next = false;
+        hipLaunchKernelGGL((adj_velocity<ND, L, true>), vgrid, block, 0, st, A);
+        if (with_a0)
+            hipLaunchKernelGGL((adj_pressure<ND, L, true>), grid, block, 0, st, A);
+        else
+            hipLaunchKernelGGL((adj_pressure<ND, L, false>), grid, block, 0, st, A);
+        if (sources)
+            hipLaunchKernelGGL(adj_sources, dim3((src.n + 255) / 256), dim3(256), 0, st, b.pq, src, step - 1);
     }
+    *pp_next = with_a0;
     return hipGetLastError();
 }
 
@@ -388,22 +708,22 @@ hipError_t launch_adjoint_step(const StepArgs &f, const SparseArgs &src, const S
                                bool *pp_next)
 {
     switch (f.geo.ndim * 8 + L) {            // L = 1..8
-    case 2 * 8 + 1: return adjoint_step_points<2, 1>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
-    case 2 * 8 + 2: return adjoint_step_points<2, 2>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
-    case 2 * 8 + 3: return adjoint_step_points<2, 3>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
-    case 2 * 8 + 4: return adjoint_step_points<2, 4>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
-    case 3 * 8 + 1: return adjoint_step_points<3, 1>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
-    case 3 * 8 + 2: return adjoint_step_points<3, 2>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
-    case 3 * 8 + 3: return adjoint_step_points<3, 3>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
-    case 3 * 8 + 4: return adjoint_step_points<3, 4>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
-    case 2 * 8 + 5: return adjoint_step_points<2, 5>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
-    case 2 * 8 + 6: return adjoint_step_points<2, 6>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
-    case 2 * 8 + 7: return adjoint_step_points<2, 7>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
-    case 2 * 8 + 8: return adjoint_step_points<2, 8>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
-    case 3 * 8 + 5: return adjoint_step_points<3, 5>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
-    case 3 * 8 + 6: return adjoint_step_points<3, 6>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
-    case 3 * 8 + 7: return adjoint_step_points<3, 7>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
-    case 3 * 8 + 8: return adjoint_step_points<3, 8>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
+    case 2 * 8 + 1: return adjoint_step<2, 1>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
+    case 2 * 8 + 2: return adjoint_step<2, 2>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
+    case 2 * 8 + 3: return adjoint_step<2, 3>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
+    case 2 * 8 + 4: return adjoint_step<2, 4>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
+    case 3 * 8 + 1: return adjoint_step<3, 1>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
+    case 3 * 8 + 2: return adjoint_step<3, 2>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
+    case 3 * 8 + 3: return adjoint_step<3, 3>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
+    case 3 * 8 + 4: return adjoint_step<3, 4>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
+    case 2 * 8 + 5: return adjoint_step<2, 5>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
+    case 2 * 8 + 6: return adjoint_step<2, 6>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
+    case 2 * 8 + 7: return adjoint_step<2, 7>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
+    case 2 * 8 + 8: return adjoint_step<2, 8>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
+    case 3 * 8 + 5: return adjoint_step<3, 5>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
+    case 3 * 8 + 6: return adjoint_step<3, 6>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
+    case 3 * 8 + 7: return adjoint_step<3, 7>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
+    case 3 * 8 + 8: return adjoint_step<3, 8>(f, src, rcv, state, state_prev, b, step, have_pp, residual, st, pp_next);
     default: return hipErrorInvalidValue;
     }
 }
