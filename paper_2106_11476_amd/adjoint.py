@@ -90,6 +90,11 @@ def _misfit_function():
             # copied into seg[0], the others recomputed from it out of place
             # (fixed buffers, so every full segment replays one HIP graph)
             seg = dom.new_state_buffer(K)
+            # the reverse steps take addresses, formed here once a step: on
+            # small grids a step's kernels take little longer than two tensor
+            # views and their pointers
+            reverse, B, base = fw2.lib().fw2_adjoint_step, dom.state_bytes(), seg.data_ptr()
+            row, width = (res.data_ptr(), res.stride(0) * 4) if res is not None else (0, 0)
             for s in reversed(range(ckpts.shape[0])):
                 n0 = s * K
                 m = min(K, n - n0)
@@ -99,8 +104,8 @@ def _misfit_function():
                     dom.set_current_step(n0)
                     dom.step_into(m - 1, seg[0], seg[1:])
                 for k in reversed(range(m)):
-                    dom.adjoint_step(seg[k], n0 + k, None if res is None else res[n0 + k],
-                                     prev=seg[k - 1] if k > 0 else None)
+                    fw2._check(reverse(dom._h, base + k * B, base + (k - 1) * B if k > 0 else None, n0 + k,
+                                       row + (n0 + k) * width if res is not None else None))
             g = dom.adjoint_gradient()
             shape, dtype, device = ctx.c_meta
             grad = g.reshape(shape).to(device=device, dtype=dtype)
