@@ -280,14 +280,14 @@ fw2_status fw2_adjoint_gradient(fw2_domain *dom, float *dst, int32_t dst_kind);
 
 /* ---- Batched stepping of many 2D domains (continuous batching) ----------
  * A batch advances several resident 2D domains of any sizes, L, memory
- * scheme and stencil mode with one launch per phase (two when domains with
- * more than four mechanisms are present: those run in a launch of their own,
- * in 256-column tiles): blocks of a fixed grid walk the tiles of every active
- * domain (the per-tile arithmetic is the single-domain sweep's,
- * so results are bitwise those of stepping each domain alone).  Each domain
- * stops by itself when its step counter reaches its own n_steps, so domains
- * with different step counts share step loops; the loop is captured as a HIP
- * graph that does not depend on which domains are active.
+ * scheme and stencil mode with one launch per phase for each class present
+ * (up to four mechanisms or more, global or per-point weights): the blocks
+ * walk the tiles of every active domain (the per-tile arithmetic is the
+ * single-domain kernels', so results are bitwise those of stepping each
+ * domain alone).  Each domain stops by itself when its step counter reaches
+ * its own n_steps, so domains with different step counts share step loops;
+ * the loop is captured as a HIP graph that does not depend on which domains
+ * are active.
  *   fw2_batch_workspace_bytes: device bytes of the batch table for up to
  *     max_domains (1..64) domains; the caller allocates them (256-byte
  *     aligned) and keeps them alive while the batch exists.
@@ -297,8 +297,9 @@ fw2_status fw2_adjoint_gradient(fw2_domain *dom, float *dst, int32_t dst_kind);
  *     back (fw2_current_step stays exact).  n = 0 empties the batch.
  *   fw2_batch_step: n steps of every active domain, asynchronously on the
  *     batch stream (the domains' own streams are not used meanwhile).
- *   fw2_batch_set_tile: tile of the batched sweep, cols = 64 or 256 columns by
- *     rows >= 1 rows; only while the batch is empty.
+ *   fw2_batch_set_tile: wanted tile, cols = 64 or 256 columns by rows >= 1
+ *     rows; only while the batch is empty.  The kernels' tiles are 64 columns
+ *     by 8 rows, or by 16 where more than 1024 points are wanted.
  * Errors: FW2_E_INVALID for bad arguments, FW2_E_UNSUPPORTED for 3D domains
  * and for domains with more than four mechanisms when the tile has 64
  * columns, FW2_E_HIP for runtime failures. */
@@ -314,7 +315,7 @@ void fw2_batch_destroy(fw2_batch *b);
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, serving loops that must not call hipMalloc, harnesses that forbid
  * it): fw2_batch_create without a workspace.  The batch uses the library's
- * own table, a file-scope device array of sizeof the 64-domain table (46 KiB,
+ * own table, a file-scope device array of sizeof the 64-domain table (48 KiB,
  * one per GPU, held until the process ends), instead of caller memory; the
  * call allocates no device memory.  max_domains is 1..64 (FW2_E_INVALID
  * beyond: the table holds 64 domains).  The table is cleared by this call

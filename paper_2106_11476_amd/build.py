@@ -13,7 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libfw2.so")
 SOURCES = [os.path.join(HERE, "csrc", f)
-           for f in ("kernels.hip", "step_p2.hip", "step_v2.hip", "step_p3.hip", "step_v3.hip", "step_f2.hip", "batch.hip",
+           for f in ("kernels.hip", "step_p2.hip", "step_v2.hip", "step_p3.hip", "step_v3.hip", "step_f2.hip", "step_t2.hip", "batch.hip",
                      "adjoint.hip", "halo.hip", "fw2.cpp", "setup.cpp")]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",
          # no packed FP32 instructions in any device code

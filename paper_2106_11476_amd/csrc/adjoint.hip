@@ -31,7 +31,7 @@
 // before is fused into the pressure kernel (A2) when its state is at hand,
 // writing that step's p'' into the second p'' buffer (this step's is still
 // read by neighbours).
-#include "kernels.hpp"
+#include "tile2d.hpp"
 
 #include <cstdio>
 #include <cstdlib>
@@ -348,35 +348,6 @@ __global__ void __launch_bounds__(kABX *kABY) adj_pressure(const AdjArgs A)
 // 1536^2, L = 4 198 / 164, L = 8 304 / 292.  Tiles of 8 rows at L <= 2, of 16
 // above: 1536^2, L = 2 105.5 / 107.3, L = 8 303 / 292.
 // ---------------------------------------------------------------------------
-
-// The most sources the tiles add themselves (each reads the list).
-constexpr int kTileSources = 4096;
-constexpr int kTX = 64;
-
-// (W x H) window of a 2D array with corner (xs, ys), loaded into registers and
-// stored to LDS; cells outside the grid are zero (the array's halo corner).
-template <int W, int H, int NT>
-struct Window {
-    static constexpr int N = (W * H + NT - 1) / NT;
-    float r[N];
-    __device__ __forceinline__ void load(const float *f, const Geometry &g, int xs, int ys, int tid)
-    {
-        const float *corner = f + (g.origin - g.pitch - 1);
-#pragma unroll
-        for (int q = 0; q < N; ++q) {
-            const int e = tid + q * NT, row = e / W, x = xs + e - row * W, y = ys + row;
-            const bool in = (unsigned)x < (unsigned)g.n[0] && (unsigned)y < (unsigned)g.n[1];
-            const uint32_t o = in ? (uint32_t)((y + 1) * (int)g.pitch + x + 1) : 0u;
-            if (e < W * H) r[q] = corner[o];
-        }
-    }
-    __device__ __forceinline__ void store(float *dst, int tid) const
-    {
-#pragma unroll
-        for (int q = 0; q < N; ++q)
-            if (tid + q * NT < W * H) dst[tid + q * NT] = r[q];
-    }
-};
 
 // D^- and D^+ from LDS: o and o2 are the strides along the axis and across it.
 __device__ __forceinline__ float tile_dminus(const float *f, const float *gw, float g11, int o, int o2)

@@ -1,6 +1,13 @@
-// Batched 2D step of many domains (continuous batching): launchers of the
-// persistent batch kernels.
-#include "step_kernels.hpp"
+// Batched 2D step of many domains (continuous batching): two launches a step
+// over the LDS tiles (tile2d.hpp) of every active entry of a device table.
+//
+// 32 domains of 128..384 points a side (2.3 M points, L = 2..4): 78.7 us a step
+// where 256-column row sweeps with a launch for the sources took 113.  What
+// that took: tiles of 64 columns (few idle lanes on narrow grids), the entry
+// found by a ballot, the entry's arguments in scalar registers and its tables
+// by global (not flat) loads, registers for four blocks a CU (85 -> 60), and
+// no launch between the phases.  8 domains (0.36 M points): 19.0 against 26.6.
+#include "tile2d.hpp"
 
 #include <mutex>
 
@@ -50,92 +57,171 @@ void release_static_batch_table(int device)
 
 namespace {
 
-// One block per entry: its sources of the current step, then (after the
-// block barrier, so the receivers see them) its receivers, then its step
-// counter advanced.
-__global__ void __launch_bounds__(256) batch_sparse(const BatchTable *__restrict__ T)
+// The entry of tile t (the last whose first tile is not past t), with what
+// decides the tile's work.  One lane per entry (a table holds at most 64) and
+// a ballot: one memory latency, where walking the entries was a chain of up
+// to 64 loads and every field another.
+static_assert(kMaxBatch <= 64, "one lane per entry");
+struct TileEntry {
+    int d, tile, nbx, key;           // entry, tile within it
+    long long step;
+    bool active;
+};
+template <bool PRESSURE>
+__device__ __forceinline__ TileEntry batch_entry_of_tile(const BatchTable *__restrict__ T, int t)
+{
+    const int lane = threadIdx.x % 64;
+    const int base = T->tile_base[lane], nbx = T->nbx[lane], key = T->key[lane];
+    const long long step = PRESSURE ? T->next[lane] : T->now[lane];
+    const bool active = step < T->n_steps[lane];
+    TileEntry r;
+    r.d = __builtin_amdgcn_readfirstlane(__popcll(__ballot(lane < T->n && base <= t)) - 1);
+    r.tile = t - __builtin_amdgcn_readlane(base, r.d);
+    r.nbx = __builtin_amdgcn_readlane(nbx, r.d);
+    r.key = __builtin_amdgcn_readlane(key, r.d);
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)step, r.d);
+    const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(step >> 32), r.d);
+    r.step = (long long)(((uint64_t)hi << 32) | lo);
+    r.active = (__ballot(active) >> r.d) & 1;
+    return r;
+}
+
+template <int TY>
+union BatchLds {
+    PressureLds<TY> p;
+    VelocityLds<TY> v;
+};
+
+template <bool PRESSURE, int L, bool C, bool PP, int TY>
+__device__ __forceinline__ void batch_tile(const BatchEntry &e, int x0, int y0, long long step, BatchLds<TY> &lds)
+{
+    const StepArgs &a = e.a;
+    if constexpr (PRESSURE) {
+        const int n_src = step < a.src.n_t && a.src.n <= kTileSources ? a.src.n : 0;
+        pressure_tile<L, C, PP, TY>(a, x0, y0, a.src, n_src, step, lds.p);
+    } else {
+        velocity_tile<L, C, PP, TY>(a, x0, y0, lds.v);
+    }
+}
+
+// Mechanism counts L0 .. L0 + 3 and both memory-variable schemes:
+// key = (L - L0) * 2 + scheme (batch_key).
+template <bool PRESSURE, int L0, bool PP, int TY>
+__device__ __forceinline__ void batch_dispatch(int key, const BatchEntry &e, int x0, int y0, long long step,
+                                               BatchLds<TY> &lds)
+{
+    switch (key) {
+#define FW2_BCASE(K, DL, C) \
+    case K: batch_tile<PRESSURE, L0 + DL, C, PP, TY>(e, x0, y0, step, lds); break;
+    FW2_BCASE(0, 0, false) FW2_BCASE(1, 0, true) FW2_BCASE(2, 1, false) FW2_BCASE(3, 1, true)
+    FW2_BCASE(4, 2, false) FW2_BCASE(5, 2, true) FW2_BCASE(6, 3, false) FW2_BCASE(7, 3, true)
+#undef FW2_BCASE
+    default: break;
+    }
+}
+
+// One phase of the entries of one class of the table: CLASS bit 0 set for
+// 5..8 mechanisms (else 1..4), bit 1 set for per-point stencil weights.
+// Each class present gets a launch of its own, so that the larger register
+// demand of many mechanisms or per-point weights does not lower the
+// occupancy of the common class; entries are grouped by class, and each
+// launch walks only its class's range of the tile list.  The first `extra`
+// blocks (one per entry, in one of the phase's launches) keep the steps: in
+// the pressure phase they copy next to now, which the velocity phase's tiles
+// read; in the velocity phase they record the entry's receivers and move next
+// and the domain's counter past the step, which no tile of that phase reads.
+// T and W are the same table: the tiles read it through T, const, so that an
+// entry's arguments load into scalar registers; only the extra blocks of the
+// pressure phase write to it, a field that its tiles do not read.
+template <bool PRESSURE, int TY, int CLASS>
+__global__ void __launch_bounds__(kTX *TY, CLASS == 0 ? 8 : 4) batch_phase(const BatchTable *__restrict__ T, BatchTable *W, int extra)
+{
+    constexpr bool MANY = (CLASS & 1) != 0, PP = (CLASS & 2) != 0;
+    if ((int)blockIdx.x < extra) {
+        if ((int)blockIdx.x >= T->n) return;
+        const int d = blockIdx.x;
+        if (PRESSURE) {
+            if (threadIdx.x == 0) W->now[d] = W->next[d];
+            return;
+        }
+        const SparseArgs &r = T->e[d].rcv;
+        const long long step = T->now[d];
+        if (step < T->n_steps[d] && step < r.cap)
+            for (int k = threadIdx.x; k < r.n; k += kTX * TY)
+                r.trace[step * r.n + k] = r.p[padded_index(r.geo, r.idx[k])];
+        if (threadIdx.x == 0) {
+            r.step[0] = step + 1;
+            W->next[d] = step + 1;
+        }
+        return;
+    }
+    __shared__ BatchLds<TY> lds;
+    // the class's own tiles: entries are grouped by class, so they are one
+    // contiguous range of the tile list
+    const int begin = T->class_begin[CLASS], total = T->class_end[CLASS] - begin;
+    // Blocks are dealt to the 8 XCDs round-robin; the blocks of XCD x take one
+    // contiguous eighth of the range (the grid is a multiple of 8), so
+    // neighbouring tiles (which share halo rows) meet in the same L2.
+    const int b = (int)blockIdx.x - extra, grid = (int)gridDim.x - extra;
+    const int x = b % 8, q = total / 8, rem = total % 8;
+    const int start = x * q + min(x, rem), end = start + q + (x < rem ? 1 : 0);
+    for (int t = start + b / 8; t < end; t += grid / 8) {
+        const TileEntry e = batch_entry_of_tile<PRESSURE>(T, begin + t);
+        if (!e.active) continue;                    // finished (uniform over the block)
+        // the entry's arguments are read in place: the address is uniform
+        // over the block, so they load into scalar registers as a kernel's
+        // own arguments do
+        batch_dispatch<PRESSURE, MANY ? 5 : 1, PP, TY>(e.key, T->e[e.d], (e.tile % e.nbx) * kTX, (e.tile / e.nbx) * TY,
+                                                       e.step, lds);
+        __syncthreads();                            // the LDS is reused by the next tile
+    }
+}
+
+// Sources of the entries that have more than the tiles take (one block each).
+__global__ void __launch_bounds__(256) batch_sources(const BatchTable *__restrict__ T)
 {
     const int d = blockIdx.x;
     if (d >= T->n) return;
-    const BatchEntry &e = T->e[d];
-    const long long step = *e.rcv.step;             // the entry's one counter (sources share it)
-    if (step < e.n_steps && step < e.a.src.n_t)
-        for (int q = threadIdx.x; q < e.a.src.n; q += blockDim.x) {
-            const int64_t pi = padded_index(e.a.src.geo, e.a.src.idx[q]);
-            e.a.src.p[pi] = e.a.src.p[pi] + e.a.src.w[q] * e.a.src.signals[(int64_t)e.a.src.sig[q] * e.a.src.n_t + step];
-        }
-    __syncthreads();
-    if (step < e.n_steps && step < e.rcv.cap)
-        for (int r = threadIdx.x; r < e.rcv.n; r += blockDim.x)
-            e.rcv.trace[step * e.rcv.n + r] = e.rcv.p[padded_index(e.rcv.geo, e.rcv.idx[r])];
-    __syncthreads();
-    if (threadIdx.x == 0) e.rcv.step[0] = step + 1;
+    const SparseArgs &s = T->e[d].a.src;
+    const long long step = T->now[d];
+    if (s.n <= kTileSources || step >= T->n_steps[d] || step >= s.n_t) return;
+    for (int q = threadIdx.x; q < s.n; q += blockDim.x) {
+        const int64_t pi = padded_index(s.geo, s.idx[q]);
+        s.p[pi] = s.p[pi] + s.w[q] * s.signals[(int64_t)s.sig[q] * s.n_t + step];
+    }
+}
+
+template <bool PRESSURE, int TY>
+void launch_batch_phase(BatchTable *T, int n_entries, unsigned blocks, hipStream_t st)
+{
+    int extra = n_entries;                          // with the phase's first launch
+#define FW2_CLASS(C)                                                                                          \
+    if (const unsigned n = batch_blocks(blocks, C)) {                                                         \
+        hipLaunchKernelGGL((batch_phase<PRESSURE, TY, C>), dim3(n + extra), dim3(kTX * TY), 0, st, T, T, extra); \
+        extra = 0;                                                                                            \
+    }
+    FW2_CLASS(0) FW2_CLASS(1) FW2_CLASS(2) FW2_CLASS(3)
+#undef FW2_CLASS
+}
+
+template <int TY>
+void launch_batch_rows(BatchTable *T, int n_entries, bool sources, unsigned blocks, hipStream_t st)
+{
+    launch_batch_phase<true, TY>(T, n_entries, blocks, st);
+    if (sources) hipLaunchKernelGGL(batch_sources, dim3(n_entries), dim3(256), 0, st, T);
+    launch_batch_phase<false, TY>(T, n_entries, blocks, st);
 }
 
 }  // namespace
 
-// Persistent grid of a batch kernel: as many blocks as fit on the device at
-// once (occupancy query), rounded down to a multiple of 8 XCDs, so that no
-// block waits for a free slot while others hold tiles.
-template <bool PRESSURE, int BX, int CLASS>
-int batch_grid()
+hipError_t launch_batch_step(const BatchTable *T, int n_entries_max, int tile, unsigned blocks, hipStream_t st)
 {
-    static const int grid = [] {
-        int dev = 0, cus = 0, per_cu = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch_phase<PRESSURE, BX, CLASS>, BX, 0) !=
-                hipSuccess ||
-            cus <= 0 || per_cu <= 0)
-            return 2048;
-        const int g = cus * per_cu;
-        return g >= 8 ? g - g % 8 : g;
-    }();
-    return grid;
-}
-
-template <bool PRESSURE, int BX, int CLASS>
-void launch_batch_class(const BatchTable *T, hipStream_t st)
-{
-    hipLaunchKernelGGL((batch_phase<PRESSURE, BX, CLASS>), dim3(batch_grid<PRESSURE, BX, CLASS>()), dim3(BX), 0, st, T);
-}
-
-template <bool PRESSURE>
-void launch_batch_phase(const BatchTable *T, int bx, unsigned classes, hipStream_t st)
-{
-    if (bx == 64) {                                 // classes 0 and 2 (at most 4 mechanisms)
-        if (classes & 1u) launch_batch_class<PRESSURE, 64, 0>(T, st);
-        if (classes & 4u) launch_batch_class<PRESSURE, 64, 2>(T, st);
-        return;
-    }
-    if (classes & 1u) launch_batch_class<PRESSURE, 256, 0>(T, st);
-    if (classes & 2u) launch_batch_class<PRESSURE, 256, 1>(T, st);
-    if (classes & 4u) launch_batch_class<PRESSURE, 256, 2>(T, st);
-    if (classes & 8u) launch_batch_class<PRESSURE, 256, 3>(T, st);
-}
-
-hipError_t launch_batch_step(const BatchTable *T, int n_entries_max, int bx, unsigned classes, hipStream_t st)
-{
-    launch_batch_phase<true>(T, bx, classes, st);
-    hipLaunchKernelGGL(batch_sparse, dim3(n_entries_max), dim3(256), 0, st, T);
-    launch_batch_phase<false>(T, bx, classes, st);
+    BatchTable *t = const_cast<BatchTable *>(T);
+    if ((tile & ~kBatchSources) == 8)
+        launch_batch_rows<8>(t, n_entries_max, (tile & kBatchSources) != 0, blocks, st);
+    else
+        launch_batch_rows<16>(t, n_entries_max, (tile & kBatchSources) != 0, blocks, st);
     return hipGetLastError();
-}
-
-void prepare_batch_launches()
-{
-    (void)batch_grid<true, 64, 0>();
-    (void)batch_grid<true, 64, 2>();
-    (void)batch_grid<false, 64, 0>();
-    (void)batch_grid<false, 64, 2>();
-    (void)batch_grid<true, 256, 0>();
-    (void)batch_grid<true, 256, 1>();
-    (void)batch_grid<true, 256, 2>();
-    (void)batch_grid<true, 256, 3>();
-    (void)batch_grid<false, 256, 0>();
-    (void)batch_grid<false, 256, 1>();
-    (void)batch_grid<false, 256, 2>();
-    (void)batch_grid<false, 256, 3>();
 }
 
 }  // namespace fw2

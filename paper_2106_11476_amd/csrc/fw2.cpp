@@ -123,8 +123,6 @@ fw2_status validate_scalars(const fw2_domain_desc *d)
 // (255 MiB) 64.8 / 54.7; 2000^2, L = 1 (269 MiB) 72.8 / 74.0; past it 1700^2,
 // L = 2 (283 MiB) 70.2 / 79.3, 1400^2, L = 4 (325 MiB) 74.1 / 86.8.
 constexpr int64_t kOneLaunchBytes = (int64_t)264 << 20;
-// The most sources a one-launch step takes (every tile reads the list).
-constexpr int32_t kOneLaunchSources = 4096;
 
 bool one_launch_size(const fw2_domain_desc *d, int64_t stride)
 {
@@ -220,16 +218,6 @@ fw2::KernelConfig sweep3d_config(const fw2::Geometry &g, int L)
     return best;
 }
 
-// Rows per block of the two-phase 2D sweeps: a block waits for memory once a
-// row, so grids of few tiles take fewer rows (us per step: 480^2, L = 2, 240
-// tiles of 4 rows: 17.1 with 4, 13.6 with 2, 13.2 with 1; 700 x 650, 489
-// tiles: 21.3, 19.7, 22.0; 900 x 1000, L = 3, 1000 tiles: 35.4, 38.5, 41.6).
-int sweep2d_rows(const fw2::Geometry &g)
-{
-    const int64_t tiles = (int64_t)((g.n[0] + 255) / 256) * ((g.n[1] + 3) / 4);
-    return tiles <= 256 ? 1 : (tiles <= 512 ? 2 : 4);
-}
-
 // (A, B0, B1) of the multipliers rho0 (1 + A kappa0 p), kappa0 (1 + kappa0 B p).
 void nl_coefficients(const fw2_domain_desc *d, double *A, double *B0, double *B1)
 {
@@ -302,9 +290,21 @@ namespace {
 
 // The velocity sweeps record the receivers in an extra block of their
 // launch; the one-thread-per-point kernel leaves them to a launch of their own.
+// Whether the pressure phase's tiles add the sources.  Every tile reads the
+// list: 21 M (tile, source) pairs cost 12 us a step (1280 sources at 4096 x
+// 2048), the launch that adds them otherwise 4.5 us, so up to 4 M pairs.
+constexpr int64_t kScanPairs = (int64_t)4 << 20;
+bool phase_adds_sources(const fw2_domain *d)
+{
+    const fw2::Geometry &g = d->ly.geo;
+    const int64_t tiles = (int64_t)((g.n[0] + 63) / 64) * ((g.n[1] + 7) / 8);
+    return d->kc.variant == 5 && d->src.n <= fw2::kTileSources && tiles * d->src.n <= kScanPairs;
+}
+
 void sync_sparse_args(fw2_domain *d)
 {
     d->args.src = d->src;
+    if (!phase_adds_sources(d)) d->args.src.n = 0;
     d->args.rcv = d->rcv;
     if (d->kc.variant == 0) d->args.rcv.step = nullptr;
 }
@@ -327,7 +327,7 @@ fw2_status enqueue_step(fw2_domain *d, TimingSlot *ts)
     if (ts) FW2_HIP(hipEventRecord(ts->ev[0], d->stream));
     FW2_HIP(fw2::launch_pressure(d->args, L, sch, d->kc, d->stream));
     if (ts) FW2_HIP(hipEventRecord(ts->ev[1], d->stream));
-    FW2_HIP(fw2::launch_sources(d->src, d->stream));
+    if (!phase_adds_sources(d)) FW2_HIP(fw2::launch_sources(d->src, d->stream));
     if (!d->args.rcv.step) FW2_HIP(fw2::launch_receivers(d->rcv, d->stream));
     if (ts) FW2_HIP(hipEventRecord(ts->ev[2], d->stream));
     FW2_HIP(fw2::launch_velocity(d->args, L, sch, d->kc, d->stream));
@@ -337,7 +337,7 @@ fw2_status enqueue_step(fw2_domain *d, TimingSlot *ts)
 
 // Whether steps run as one launch each: decided by the grid when the domain
 // is created and by the number of sources; kernel timing takes the phases.
-bool one_launch(const fw2_domain *d) { return d->one.variant == 4 && !d->timing && d->src.n <= kOneLaunchSources; }
+bool one_launch(const fw2_domain *d) { return d->one.variant == 4 && !d->timing && d->src.n <= fw2::kTileSources; }
 
 // Step k of a run of one-launch steps from the state block at src to that at
 // dst: its sources are those k past the device counter, and it records the
@@ -353,6 +353,7 @@ fw2_status enqueue_one_launch(fw2_domain *d, int32_t k, const float *src, float 
     a.psi1 = a.p + (int64_t)(1 + nd) * S;
     a.psi2 = a.psi1 + (int64_t)nd * L * S;
     a.out = ((int64_t)(uintptr_t)dst - (int64_t)(uintptr_t)src) / 4;   // both 4-byte aligned
+    a.src = d->src;
     a.src.off = k;
     a.rcv.off = k - 1;
     a.rcv.p = a.p;
@@ -373,7 +374,7 @@ fw2_status enqueue_step_on(fw2_domain *d, hipStream_t s)
 {
     const int L = d->desc.n_relax, sch = d->desc.relax_scheme;
     FW2_HIP(fw2::launch_pressure(d->args, L, sch, d->kc, s));
-    FW2_HIP(fw2::launch_sources(d->src, s));
+    if (!phase_adds_sources(d)) FW2_HIP(fw2::launch_sources(d->src, s));
     if (!d->args.rcv.step) FW2_HIP(fw2::launch_receivers(d->rcv, s));
     FW2_HIP(fw2::launch_velocity(d->args, L, sch, d->kc, s));
     return FW2_OK;
@@ -780,13 +781,13 @@ fw2_status fw2_create_domain(const fw2_domain_desc *desc, void *dev_workspace, u
         a.w1[ax] = a.w2[ax] = nullptr;
     }
 
-    d->kc = nd == 2 ? fw2::KernelConfig{1, 256, sweep2d_rows(g)} : sweep3d_config(g, L);
+    d->kc = nd == 2 ? fw2::KernelConfig{5, 64, 8} : sweep3d_config(g, L);
     if (ly.shadow) d->one = fw2::KernelConfig{4, 64, one_launch_rows(g, L)};
     if (const char *ev = std::getenv("FW2_KERNEL_CONFIG")) {      // "variant,bx,rows[,by]" (tuning runs)
         int v = 0, bx = 0, ry = 0, by = 0;
         const int nparsed = std::sscanf(ev, "%d,%d,%d,%d", &v, &bx, &ry, &by);
         const bool parsed = nparsed == 3 || nparsed == 4;
-        const bool ok2 = nd == 2 && by == 0 && (v == 0 || v == 1 || v == 2) && (bx == 64 || bx == 128 || bx == 256);
+        const bool ok2 = nd == 2 && by == 0 && (v == 0 || (v == 5 && (ry == 8 || ry == 16))) && (bx == 64 || bx == 128 || bx == 256);
         if (parsed && v == 4 && by == 0 && ly.shadow && (ry == 8 || ry == 12 || ry == 16)) d->one = fw2::KernelConfig{4, bx, ry};
         const bool tile3 = by == 0 ? (bx == 16 || bx == 32 || bx == 64)
                                    : (v == 3 && ((bx == 64 && by == 4) || (bx == 32 && by == 8)));
@@ -1032,7 +1033,7 @@ fw2_status enqueue_step_into(fw2_domain *d, const float *src, float *dst, hipStr
     rcv.p = dst;
     a.p = dst;
     a.rcv.p = dst;
-    FW2_HIP(fw2::launch_sources(src_pts, s));
+    if (!phase_adds_sources(d)) FW2_HIP(fw2::launch_sources(src_pts, s));
     if (!a.rcv.step) FW2_HIP(fw2::launch_receivers(rcv, s));
     FW2_HIP(fw2::launch_velocity(a, L, sch, d->kc, s));
     return FW2_OK;
@@ -1266,7 +1267,7 @@ fw2_status fw2_step_phase(fw2_domain *d, int32_t phase)
     if (phase == FW2_PHASE_PRESSURE) {
         if (d->mid_step) return fail(FW2_E_STATE, "the pressure phase of this step already ran");
         FW2_HIP(fw2::launch_pressure(d->args, L, sch, d->kc, d->stream));
-        FW2_HIP(fw2::launch_sources(d->src, d->stream));
+        if (!phase_adds_sources(d)) FW2_HIP(fw2::launch_sources(d->src, d->stream));
         d->mid_step = true;
         return FW2_OK;
     }
@@ -1308,11 +1309,18 @@ struct fw2_batch {
     int graph_chunk = 32;
     int rows = 4;
     int bx = 256;
-    unsigned classes = 0;               // launch classes present in the table (fw2::batch_class)
+    unsigned blocks = 0;                // blocks of each class launch (fw2::batch_code)
+    bool sources = false;               // an entry has more sources than the tiles add
     int static_device = -1;             // >= 0: the table is the library's own on this device
 };
 
 namespace {
+
+// Tile rows: the batched kernels have tiles of 64 columns by 8 or 16 rows, a
+// requested tile of more than 1024 points takes 16.
+int tile_rows(const fw2_batch *b) { return b->bx * b->rows > 1024 ? 16 : 8; }
+
+int batch_tile(const fw2_batch *b) { return tile_rows(b) | (b->sources ? fw2::kBatchSources : 0); }
 
 void batch_drop_graph(fw2_batch *b)
 {
@@ -1328,7 +1336,7 @@ fw2_status batch_build_graph(fw2_batch *b)
     FW2_HIP(hipStreamBeginCapture(b->capture, hipStreamCaptureModeThreadLocal));
     hipError_t e = hipSuccess;
     for (int k = 0; k < b->graph_chunk && e == hipSuccess; ++k)
-        e = fw2::launch_batch_step(b->dev, b->max_domains, b->bx, b->classes, b->capture);
+        e = fw2::launch_batch_step(b->dev, b->max_domains, batch_tile(b), b->blocks, b->capture);
     hipGraph_t graph = nullptr;
     hipError_t e2 = hipStreamEndCapture(b->capture, &graph);
     if (e != hipSuccess || e2 != hipSuccess) {
@@ -1380,7 +1388,6 @@ fw2_status fw2_batch_create(int32_t max_domains, void *dev_workspace, uint64_t w
     if (workspace_bytes < need) return fail(FW2_E_NOMEM, "batch workspace too small");
     fw2_batch *b = new (std::nothrow) fw2_batch();
     if (!b) return fail(FW2_E_NOMEM, "host allocation failed");
-    fw2::prepare_batch_launches();
     b->max_domains = max_domains;
     b->dev = (fw2::BatchTable *)dev_workspace;
     b->stream = (hipStream_t)stream;
@@ -1417,10 +1424,10 @@ fw2_status fw2_batch_set_domains(fw2_batch *b, int32_t n, fw2_domain *const *dom
     std::memset(&T, 0, sizeof(T));
     T.rows = b->rows;
     int tiles = 0, m = 0;
-    unsigned classes = 0;
+    bool sources = false;
     for (int32_t k = 0; k < n; ++k) {
         fw2_domain *d = domains[k];
-        classes |= 1u << fw2::batch_class(d->desc.n_relax, d->args.local_stencil);
+        sources |= d->src.n > fw2::kTileSources;
         // the domain's own queued work must be finished before the batch stream touches it
         FW2_HIP(hipStreamSynchronize(d->stream));
         b->doms.push_back(d);
@@ -1433,25 +1440,38 @@ fw2_status fw2_batch_set_domains(fw2_batch *b, int32_t n, fw2_domain *const *dom
         for (int32_t k = 0; k < n; ++k) {
             fw2_domain *d = domains[k];
             if (fw2::batch_class(d->desc.n_relax, d->args.local_stencil) != c) continue;
-            fw2::BatchEntry &e = T.e[m++];
-            e.a = d->args;
-            e.rcv = d->rcv;
-            e.n_steps = n_steps[k];
-            e.L = d->desc.n_relax;
-            e.scheme = d->desc.relax_scheme;
-            const int nbx = (d->ly.geo.n[0] + b->bx - 1) / b->bx;
-            const int nby = (d->ly.geo.n[1] + b->rows - 1) / b->rows;
-            e.tiles = nbx * nby;
-            e.tile_base = tiles;
-            tiles += e.tiles;
+            T.e[m].a = d->args;
+            T.e[m].a.src = d->src;
+            T.e[m].rcv = d->rcv;
+            const int ty = tile_rows(b);
+            T.tile_base[m] = tiles;
+            T.nbx[m] = (d->ly.geo.n[0] + 63) / 64;
+            T.key[m] = fw2::batch_key(d->desc.n_relax, d->desc.relax_scheme);
+            T.n_steps[m] = n_steps[k];
+            T.next[m] = d->step;
+            tiles += T.nbx[m] * ((d->ly.geo.n[1] + ty - 1) / ty);
+            m++;
         }
         T.class_end[c] = tiles;
     }
     if (m != n) return fail(FW2_E_INVALID, "a domain of no launch class");
     T.n = n;
     T.total_tiles = tiles;
-    if (classes != b->classes) batch_drop_graph(b);    // the captured launches differ
-    b->classes = classes;
+    // the captured grids stay while every class has tiles as before and fills
+    // at least half of its blocks (a block without a tile ends at once)
+    bool fits = b->sources == sources;
+    unsigned blocks = 0;
+    for (int c = 0; c < 4; ++c) {
+        const unsigned need = (unsigned)(T.class_end[c] - T.class_begin[c]), have = fw2::batch_blocks(b->blocks, c);
+        const unsigned code = fw2::batch_code((int)need, c);
+        fits = fits && (code == (b->blocks & (255u << (8 * c))) || (need > 0 && need <= have && 2 * need >= have));
+        blocks |= code;
+    }
+    if (!fits && n > 0) {
+        batch_drop_graph(b);
+        b->blocks = blocks;
+        b->sources = sources;
+    }
     FW2_HIP(hipMemcpyAsync(b->dev, &T, sizeof(T), hipMemcpyHostToDevice, b->stream));
     FW2_HIP(hipStreamSynchronize(b->stream));
     return FW2_OK;
@@ -1470,7 +1490,8 @@ fw2_status fw2_batch_step(fw2_batch *b, int32_t n)
         }
         for (; left >= b->graph_chunk; left -= b->graph_chunk) FW2_HIP(hipGraphLaunch(b->graph, b->stream));
     }
-    for (; left > 0; --left) FW2_HIP(fw2::launch_batch_step(b->dev, b->max_domains, b->bx, b->classes, b->stream));
+    for (; left > 0; --left)
+        FW2_HIP(fw2::launch_batch_step(b->dev, b->max_domains, batch_tile(b), b->blocks, b->stream));
     for (size_t k = 0; k < b->doms.size(); ++k)
         b->doms[k]->step = std::min<int64_t>(b->doms[k]->step + n, b->target[k]);
     return FW2_OK;
@@ -1482,9 +1503,10 @@ fw2_status fw2_batch_set_tile(fw2_batch *b, int32_t cols, int32_t rows)
     if (rows < 1 || rows > 1024) return fail(FW2_E_INVALID, "rows must be in 1..1024");
     if (cols != 64 && cols != 256) return fail(FW2_E_INVALID, "cols must be 64 or 256");
     if (!b->doms.empty()) return fail(FW2_E_STATE, "set the tile while the batch is empty");
-    if (cols != b->bx) batch_drop_graph(b);
+    const int before = tile_rows(b);
     b->bx = cols;
     b->rows = rows;
+    if (tile_rows(b) != before) batch_drop_graph(b);
     b->host.rows = rows;
     FW2_HIP(hipMemcpy(b->dev, &b->host, sizeof(b->host), hipMemcpyHostToDevice));
     return FW2_OK;
@@ -1507,7 +1529,6 @@ fw2_status fw2_batch_create_noalloc(int32_t max_domains, void *stream, fw2_batch
         fw2::release_static_batch_table(device);
         return fail(FW2_E_NOMEM, "host allocation failed");
     }
-    fw2::prepare_batch_launches();
     b->max_domains = max_domains;
     b->dev = table;
     b->static_device = device;

@@ -54,11 +54,13 @@ __global__ void check_kernel(const float *p, const Geometry g, float limit, int 
 hipError_t launch_pressure(const StepArgs &a, int L, int scheme, const KernelConfig &kc, hipStream_t st)
 {
     if (kc.variant == 4) return launch_fused_2d(a, L, scheme, kc, st);
+    if (kc.variant == 5) return launch_tiles_2d(a, L, scheme, true, kc.rows, st);
     return a.geo.ndim == 2 ? launch_pressure_2d(a, L, scheme, kc, st) : launch_pressure_3d(a, L, scheme, kc, st);
 }
 
 hipError_t launch_velocity(const StepArgs &a, int L, int scheme, const KernelConfig &kc, hipStream_t st)
 {
+    if (kc.variant == 5) return launch_tiles_2d(a, L, scheme, false, kc.rows, st);
     return a.geo.ndim == 2 ? launch_velocity_2d(a, L, scheme, kc, st) : launch_velocity_3d(a, L, scheme, kc, st);
 }
 

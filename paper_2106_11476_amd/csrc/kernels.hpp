@@ -93,16 +93,15 @@ struct StepArgs {
 
 // Kernel variant and tile shape.  variant 0: one thread per point over a
 // (64 x 8) tile, every stencil tap a cached global load (any ndim).
-// variant 1 (2D): row sweeps of `bx` columns x `rows` rows with a register
-// window along y and LDS rings along x; variant 2: the same with the next
-// row's loads issued before the current row is computed.  variant 1 (3D):
-// plane sweeps of a column tile (32x16, 64x8 or 16x16 for bx = 32, 64, 16)
-// over `rows` planes with a register window along z and LDS plane rings;
-// variant 2 (3D): the same with every load of the next plane issued during
-// the current one; variant 3 (3D): only the staged planes and the z window
-// one plane ahead, the point's own values at the top of their plane.
-// variant 4 (2D, at most four mechanisms): a whole step out of place in one
-// launch of 64 x `rows` tiles (step_f2.hip), passed to launch_pressure.
+// 3D: variant 1, plane sweeps of a column tile (32x16, 64x8 or 16x16 for bx =
+// 32, 64, 16) over `rows` planes with a register window along z and LDS plane
+// rings; variant 2, the same with every load of the next plane issued during
+// the current one; variant 3, only the staged planes and the z window one
+// plane ahead, the point's own values at the top of their plane.
+// 2D: variant 4 (at most four mechanisms), a whole step out of place in one
+// launch of 64 x `rows` tiles (step_f2.hip), passed to launch_pressure;
+// variant 5, the phases from LDS tiles of 64 x `rows` (step_t2.hip), the
+// pressure phase adding the sources in a.src.
 struct KernelConfig {
     int variant;
     int bx;
@@ -111,27 +110,33 @@ struct KernelConfig {
 };
 
 // Many 2D domains advanced by one launch per phase (batched serving).  The
-// table lives in device memory; blocks of a fixed, persistent grid walk all
-// tiles of all entries, so a captured step loop does not depend on which
+// table lives in device memory; the blocks of a grid sized for the tiles of
+// all entries walk them, so a captured step loop does not depend on which
 // domains are active.  A domain whose step counter has reached n_steps is
 // skipped (its counter keeps counting while it stays in the table).
 constexpr int kMaxBatch = 64;
+// The most sources the tiles of a 2D kernel add themselves (each reads the
+// list); more are added by a launch of their own.
+constexpr int32_t kTileSources = 4096;
 
 struct BatchEntry {
     StepArgs a;
     SparseArgs rcv;          // (the sources are a.src)
-    long long n_steps;
-    int32_t L, scheme;
-    int32_t tile_base, tiles;        // tiles of bx columns x rows
 };
 
 struct BatchTable {
     int32_t n;
     int32_t total_tiles;
-    int32_t rows;                    // tile rows; tile columns bx = 64 or 256
+    int32_t rows;                    // tile rows
     // Entries are ordered by launch class; the tiles of class c are
     // [class_begin[c], class_end[c]) of the tile list.
     int32_t class_begin[4], class_end[4];
+    // What a block needs to find its tile's entry and whether it is active,
+    // one lane per entry: the first tile, tiles per row, mechanisms and memory
+    // scheme (batch_key), the step to stop at, the next step (the device
+    // counter's value between steps) and the step under way.
+    int32_t tile_base[kMaxBatch], nbx[kMaxBatch], key[kMaxBatch];
+    long long n_steps[kMaxBatch], next[kMaxBatch], now[kMaxBatch];
     BatchEntry e[kMaxBatch];
 };
 
@@ -142,13 +147,30 @@ __host__ __device__ inline int batch_class(int L, int local_stencil)
     return (L > 4 ? 1 : 0) | (local_stencil ? 2 : 0);
 }
 
-// One step of every entry.  classes: bit c set when the table holds entries
-// of class c (classes 1 and 3 need bx = 256).
-hipError_t launch_batch_step(const BatchTable *dev_table, int n_entries_max, int bx, unsigned classes,
+// Mechanisms 1..4 or 5..8 (by class) and scheme of an entry.
+inline int batch_key(int L, int scheme) { return ((L - 1) % 4) * 2 + scheme; }
+
+// Blocks of each class launch, a byte per class: 0 for none, else a count
+// (8 + m) << e as e * 8 + m + 1, at least the class's tiles (and at most 1/8
+// over; every count is a multiple of 8).
+inline unsigned batch_blocks(unsigned code, int c)
+{
+    const unsigned v = (code >> (8 * c)) & 255u;
+    return v == 0 ? 0u : (8u + (v - 1u) % 8u) << ((v - 1u) / 8u);
+}
+inline unsigned batch_code(int tiles, int c)
+{
+    if (tiles <= 0) return 0;
+    for (unsigned v = 3 * 8 + 1;; ++v)               // from 64 blocks up
+        if (batch_blocks(v, 0) >= (unsigned)tiles) return v << (8 * c);
+}
+
+// One step of every entry.  tile: the tile rows (8 or 16), with kBatchSources
+// where an entry has more sources than the tiles add; blocks: batch_code of
+// every class, or-ed.
+constexpr int kBatchSources = 256;
+hipError_t launch_batch_step(const BatchTable *dev_table, int n_entries_max, int tile, unsigned blocks,
                              hipStream_t stream);
-// Sizes the persistent grids of the batch kernels (occupancy queries); call
-// outside stream capture before the first batched step.
-void prepare_batch_launches();
 // The library's own batch table on `device` (the current device), for a
 // batch that allocates nothing: *busy is set (and *table left NULL) while
 // another such batch holds it.  Released by release_static_batch_table.
@@ -178,6 +200,7 @@ hipError_t launch_velocity_2d(const StepArgs &a, int L, int scheme, const Kernel
 hipError_t launch_pressure_3d(const StepArgs &a, int L, int scheme, const KernelConfig &kc, hipStream_t stream);
 hipError_t launch_velocity_3d(const StepArgs &a, int L, int scheme, const KernelConfig &kc, hipStream_t stream);
 
+hipError_t launch_tiles_2d(const StepArgs &a, int L, int scheme, bool pressure, int rows, hipStream_t stream);
 hipError_t launch_fused_2d(const StepArgs &a, int L, int scheme, const KernelConfig &kc, hipStream_t stream);
 
 // Launchers (kernels.hip).  All enqueue on `stream` and return the launch error.

@@ -14,9 +14,10 @@
 // with w, b, c from the per-axis (boundary slot, tissue label) tables.
 //
 // The work is bandwidth bound (about 1 flop per byte), so there is no MFMA:
-// threads map to consecutive x (coalesced 256-byte rows per wavefront) and
-// each thread walks several rows, the stencil taps reusing L1/L2-resident
-// neighbours.
+// threads map to consecutive x (coalesced 256-byte rows per wavefront).  This
+// file has the one-thread-per-point kernels of both dimensions (every tap a
+// load of its own, served by L1 and L2) and the 3D plane sweeps; tile2d.hpp
+// has the 2D kernels from LDS tiles.
 #pragma once
 
 #include "kernels.hpp"
@@ -195,16 +196,8 @@ __global__ void __launch_bounds__(kBX * kBY) velocity_kernel(const StepArgs a)
     }
 }
 
-// ---------------------------------------------------------------------------
-// 2D sweep kernels.  A block of BX threads owns BX consecutive columns and
-// walks `rows` rows in +y.  Each thread keeps the 8-row window of the
-// y-stencil field for its own column in registers (one new row per step);
-// rows of the x-stencil field live in small LDS rings (one barrier per row),
-// so every array is read from HBM once per launch apart from the short
-// column halo.  Tiles are numbered so that each XCD (blocks b = k mod 8)
-// takes a contiguous band of tiles, keeping halo lines in one L2.
-// ---------------------------------------------------------------------------
-
+// Tiles are numbered so that each XCD (blocks b = k mod 8) takes a contiguous
+// band of tiles, keeping halo lines in one L2.
 // A bijection of [0, nblocks) for any nblocks: the first nblocks % 8 XCDs
 // take one tile more.  (Grids whose tile count was no multiple of 8 kept the
 // plain order before and fetched their halo lines once per XCD: a 900 x 1000
@@ -259,307 +252,6 @@ __device__ __forceinline__ float ldz(const float *__restrict__ f, const Geometry
     return *at_plane(plane_base(f, g, 0), plane_point(g, x, y));
 }
 
-// LDS hand-off between the threads of a block.  A one-wavefront block needs
-// no hardware barrier (a wavefront's LDS operations complete in order); the
-// fences keep the compiler from moving LDS accesses across it, and global
-// loads of the next row stay in flight.
-template <int BX>
-__device__ __forceinline__ void lds_sync()
-{
-    if constexpr (BX == 64) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    } else {
-        __syncthreads();
-    }
-}
-
-// Column of halo lane t (t < 8) of a tile starting at x0: x0-4..x0-1 and
-// x0+BX..x0+BX+3; its slot in an LDS row whose column c holds x0 - 4 + c.
-template <int BX>
-__device__ __forceinline__ int halo_x(int t, int x0) { return t < 4 ? x0 - 4 + t : x0 + BX + (t - 4); }
-template <int BX>
-__device__ __forceinline__ int halo_c(int t) { return t < 4 ? t : BX + t; }
-
-template <int L>
-struct PRow {                 // everything the pressure sweep loads for one row
-    float vyn, vxn, hx, hy;   // window row j+3, ring row j+1, halos
-    float p0, k0, q0, r0;     // r0: rho, loaded for per-point weights only
-    int l;
-    float m[2][L];
-};
-
-template <int L, int BX, bool PP>
-__device__ __forceinline__ void p_load_row(PRow<L> &r, const StepArgs &a, int i, int t, int x0, int j, bool live)
-{
-    const Geometry &g = a.geo;
-    const float *__restrict__ vx = a.v;
-    const float *__restrict__ vy = a.v + g.stride;
-    r.vyn = ldz(vy, g, i, j + 3);
-    r.vxn = ldz(vx, g, i, j + 1);
-    r.hx = t < 8 ? ldz(vx, g, halo_x<BX>(t, x0), j + 1) : 0.0f;
-    r.hy = t < 2 ? ldz(vy, g, t == 0 ? x0 - 1 : x0 + BX, j) : 0.0f;
-    const uint32_t pt = plane_point(g, i, j);
-    if (live) {
-        r.p0 = *at_plane(plane_base(a.p, g, 0), pt);
-        r.k0 = *at_plane(plane_base(a.kap, g, 0), pt);
-        r.q0 = *at_plane(plane_base(a.nlq, g, 0), pt);
-        r.r0 = PP ? *at_plane(plane_base(a.rho, g, 0), pt) : 1.0f;
-        r.l = a.label ? label_at(plane_base(a.label, g, 0), pt) : 0;
-#pragma unroll
-        for (int ax = 0; ax < 2; ++ax)
-#pragma unroll
-            for (int nu = 0; nu < L; ++nu)
-                r.m[ax][nu] = ntld(at_plane(plane_base(a.psi2 + (int64_t)(ax * L + nu) * g.stride, g, 0), pt));
-    }
-}
-
-// One tile (columns x0..x0+BX-1, rows y0..y0+rows-1) of the 2D pressure
-// sweep; sx / sy are the block's LDS rings.
-template <int L, bool CENTRED, int BX, bool PF, bool PP>
-__device__ __forceinline__ void pressure_tile2d(const StepArgs &a, int rows, int x0, int y0,
-                                                float (*sx)[BX + 8], float (*sy)[BX + 2])
-{
-    const Geometry &g = a.geo;
-    const int t = threadIdx.x;
-    const int i = x0 + t;
-    const int nx = g.n[0], ny = g.n[1];
-    const bool live = i < nx;
-    const float *__restrict__ vx = a.v;
-    const float *__restrict__ vy = a.v + g.stride;
-    float *__restrict__ pp = a.p + a.out;        // written only
-    float *__restrict__ psi = a.psi2 + a.out;
-
-    // prologue: window rows y0-4 .. y0+2, rings rows y0-1 and y0
-    float w[8];
-    w[0] = 0.0f;
-#pragma unroll
-    for (int k = 1; k < 8; ++k) w[k] = ldz(vy, g, i, y0 - 5 + k);
-#pragma unroll
-    for (int r = -1; r <= 0; ++r) {
-        sx[(y0 + r) & 3][t + 4] = ldz(vx, g, i, y0 + r);
-        if (t < 8) sx[(y0 + r) & 3][halo_c<BX>(t)] = ldz(vx, g, halo_x<BX>(t, x0), y0 + r);
-    }
-    sy[(y0 + 2) % 3][t + 1] = ldz(vy, g, i, y0 - 1);
-    if (t < 2) sy[(y0 + 2) % 3][t == 0 ? 0 : BX + 1] = ldz(vy, g, t == 0 ? x0 - 1 : x0 + BX, y0 - 1);
-
-    const int sxs = max(max(a.nb[0] - i, i - (nx - 1 - a.nb[0])), 0);
-    const int yend = min(y0 + rows, ny);
-    PRow<L> cur, nxt;
-    if (PF) p_load_row<L, BX, PP>(cur, a, i, t, x0, y0, live);
-    for (int j = y0; j < yend; ++j) {
-        if (!PF) p_load_row<L, BX, PP>(cur, a, i, t, x0, j, live);        // rows loaded in turn
-        else if (j + 1 < yend) p_load_row<L, BX, PP>(nxt, a, i, t, x0, j + 1, live);   // next row in flight
-#pragma unroll
-        for (int k = 0; k < 7; ++k) w[k] = w[k + 1];
-        w[7] = cur.vyn;
-        sx[(j + 1) & 3][t + 4] = cur.vxn;
-        if (t < 8) sx[(j + 1) & 3][halo_c<BX>(t)] = cur.hx;
-        sy[j % 3][t + 1] = w[4];
-        if (t < 2) sy[j % 3][t == 0 ? 0 : BX + 1] = cur.hy;
-        lds_sync<BX>();
-        if (live) {
-            const Wts W = weights<PP>(a, PP ? cell_r2(a, cur.r0, cur.k0) : 0.0f);
-            const float *r0 = sx[j & 3], *rp = sx[(j + 1) & 3], *rm = sx[(j + 3) & 3];
-            float Dx = W.g0 * (r0[t + 4] - r0[t + 3]);
-            Dx = fmaf(W.g1, r0[t + 5] - r0[t + 2], Dx);
-            Dx = fmaf(W.g2, r0[t + 6] - r0[t + 1], Dx);
-            Dx = fmaf(W.g3, r0[t + 7] - r0[t], Dx);
-            Dx = fmaf(W.g11, (rp[t + 4] - rp[t + 3]) + (rm[t + 4] - rm[t + 3]), Dx);
-            const float *c0 = sy[j % 3], *cm = sy[(j + 2) % 3];
-            float Dy = W.g0 * (w[4] - w[3]);
-            Dy = fmaf(W.g1, w[5] - w[2], Dy);
-            Dy = fmaf(W.g2, w[6] - w[1], Dy);
-            Dy = fmaf(W.g3, w[7] - w[0], Dy);
-            Dy = fmaf(W.g11, (c0[t + 2] - cm[t + 2]) + (c0[t] - cm[t]), Dy);
-            const int sys = max(max(a.nb[1] - j, j - (ny - 1 - a.nb[1])), 0);
-            float S = 0.0f;
-#pragma unroll
-            for (int ax = 0; ax < 2; ++ax) {
-                const float D = ax == 0 ? Dx : Dy;
-                const int tt = (ax == 0 ? sxs : sys) * a.n_labels + cur.l;
-                const float2 *__restrict__ bc = a.bc2[ax] + (int64_t)tt * L;
-                float Sa = a.w2[ax][tt] * D;
-#pragma unroll
-                for (int nu = 0; nu < L; ++nu) {
-                    const float2 q = bc[nu];
-                    const float mn = fmaf(q.x, cur.m[ax][nu], q.y * D);
-                    Sa += CENTRED ? cur.m[ax][nu] : mn;
-                    cur.m[ax][nu] = mn;
-                }
-                S += Sa;
-            }
-            const uint32_t pt = plane_point(g, i, j);
-            const float kappa = cur.k0 * (1.0f + cur.q0 * cur.p0);
-            *at_plane_w(plane_base(pp, g, 0), pt) = cur.p0 - a.dt * S / kappa;
-#pragma unroll
-            for (int ax = 0; ax < 2; ++ax)
-#pragma unroll
-                for (int nu = 0; nu < L; ++nu)
-                    ntst(at_plane_w(plane_base(psi + (int64_t)(ax * L + nu) * g.stride, g, 0), pt), cur.m[ax][nu]);
-        }
-        if (PF) cur = nxt;
-    }
-}
-
-template <int L>
-struct VRow {                 // everything the velocity sweep loads for one row
-    float pn, rn, kn, hp, hr, hk;   // window row j+4, rho/kappa0 row j+1, halos
-    float ux, uy;
-    int l;
-    float m[2][L];
-};
-
-template <int L, int BX>
-__device__ __forceinline__ void v_load_row(VRow<L> &r, const StepArgs &a, int i, int t, int x0, int j, bool live)
-{
-    const Geometry &g = a.geo;
-    r.pn = ldz(a.p, g, i, j + 4);
-    r.rn = ldz(a.rho, g, i, j + 1);
-    r.kn = ldz(a.kap, g, i, j + 1);
-    r.hp = t < 8 ? ldz(a.p, g, halo_x<BX>(t, x0), j + 1) : 0.0f;
-    r.hr = t == 0 ? ldz(a.rho, g, x0 + BX, j + 1) : 0.0f;
-    r.hk = t == 0 ? ldz(a.kap, g, x0 + BX, j + 1) : 0.0f;
-    const uint32_t pt = plane_point(g, i, j);
-    if (live) {
-        r.ux = *at_plane(plane_base(a.v, g, 0), pt);
-        r.uy = *at_plane(plane_base(a.v + g.stride, g, 0), pt);
-        r.l = a.label ? label_at(plane_base(a.label, g, 0), pt) : 0;
-#pragma unroll
-        for (int ax = 0; ax < 2; ++ax)
-#pragma unroll
-            for (int nu = 0; nu < L; ++nu)
-                r.m[ax][nu] = ntld(at_plane(plane_base(a.psi1 + (int64_t)(ax * L + nu) * g.stride, g, 0), pt));
-    }
-}
-
-// One tile of the 2D velocity sweep; sp / sr / sk are the block's LDS rings.
-template <int L, bool CENTRED, int BX, bool PF, bool PP>
-__device__ __forceinline__ void velocity_tile2d(const StepArgs &a, int rows, int x0, int y0,
-                                                float (*sp)[BX + 8], float (*sr)[BX + 1], float (*sk)[BX + 1])
-{
-    const Geometry &g = a.geo;
-    const int t = threadIdx.x;
-    const int i = x0 + t;
-    const int nx = g.n[0], ny = g.n[1];
-    const bool live = i < nx;
-    const float *__restrict__ pp = a.p;
-    float *__restrict__ vx = a.v + a.out;        // written only
-    float *__restrict__ vy = a.v + g.stride + a.out;
-    float *__restrict__ psi = a.psi1 + a.out;
-
-    // prologue: window rows y0-3 .. y0+3; p ring rows y0-1, y0; rho/kappa row y0
-    float w[8];
-    w[0] = 0.0f;
-#pragma unroll
-    for (int k = 1; k < 8; ++k) w[k] = ldz(pp, g, i, y0 - 4 + k);
-#pragma unroll
-    for (int r = -1; r <= 0; ++r) {
-        sp[(y0 + r) & 3][t + 4] = ldz(pp, g, i, y0 + r);
-        if (t < 8) sp[(y0 + r) & 3][halo_c<BX>(t)] = ldz(pp, g, halo_x<BX>(t, x0), y0 + r);
-    }
-    sr[y0 % 3][t] = ldz(a.rho, g, i, y0);
-    sk[y0 % 3][t] = ldz(a.kap, g, i, y0);
-    if (t == 0) {
-        sr[y0 % 3][BX] = ldz(a.rho, g, x0 + BX, y0);
-        sk[y0 % 3][BX] = ldz(a.kap, g, x0 + BX, y0);
-    }
-
-    const int sxs = max(max(a.nb[0] - i, i - (nx - 2 - a.nb[0])), 0);
-    const int yend = min(y0 + rows, ny);
-    VRow<L> cur, nxt;
-    if (PF) v_load_row<L, BX>(cur, a, i, t, x0, y0, live);
-    for (int j = y0; j < yend; ++j) {
-        if (!PF) v_load_row<L, BX>(cur, a, i, t, x0, j, live);
-        else if (j + 1 < yend) v_load_row<L, BX>(nxt, a, i, t, x0, j + 1, live);
-#pragma unroll
-        for (int k = 0; k < 7; ++k) w[k] = w[k + 1];
-        w[7] = cur.pn;
-        sp[(j + 1) & 3][t + 4] = w[4];
-        if (t < 8) sp[(j + 1) & 3][halo_c<BX>(t)] = cur.hp;
-        sr[(j + 1) % 3][t] = cur.rn;
-        sk[(j + 1) % 3][t] = cur.kn;
-        if (t == 0) {
-            sr[(j + 1) % 3][BX] = cur.hr;
-            sk[(j + 1) % 3][BX] = cur.hk;
-        }
-        lds_sync<BX>();
-        if (live) {
-            const uint32_t pt = plane_point(g, i, j);
-            const float *r0 = sp[j & 3], *rp = sp[(j + 1) & 3], *rm = sp[(j + 3) & 3];
-            const float *rr0 = sr[j % 3], *kk0 = sk[j % 3];
-            const float s0 = PP ? cell_r2(a, rr0[t], kk0[t]) : 0.0f;
-            // v_x at (i + 1/2, j)
-            if (i < nx - 1) {
-                const Wts W = weights<PP>(a, PP ? 0.5f * (s0 + cell_r2(a, rr0[t + 1], kk0[t + 1])) : 0.0f);
-                float D = W.g0 * (r0[t + 5] - r0[t + 4]);
-                D = fmaf(W.g1, r0[t + 6] - r0[t + 3], D);
-                D = fmaf(W.g2, r0[t + 7] - r0[t + 2], D);
-                D = fmaf(W.g3, r0[t + 8] - r0[t + 1], D);
-                D = fmaf(W.g11, (rp[t + 5] - rp[t + 4]) + (rm[t + 5] - rm[t + 4]), D);
-                const int tt = sxs * a.n_labels + cur.l;
-                const float2 *__restrict__ bc = a.bc1[0] + (int64_t)tt * L;
-                float S = a.w1[0][tt] * D;
-#pragma unroll
-                for (int nu = 0; nu < L; ++nu) {
-                    const float2 q = bc[nu];
-                    const float mn = fmaf(q.x, cur.m[0][nu], q.y * D);
-                    S += CENTRED ? cur.m[0][nu] : mn;
-                    cur.m[0][nu] = mn;
-                }
-                const float pbar = 0.5f * (r0[t + 4] + r0[t + 5]);
-                const float rho_a = 0.5f * (rr0[t] + rr0[t + 1]);
-                const float kap_a = 0.5f * (kk0[t] + kk0[t + 1]);
-                *at_plane_w(plane_base(vx, g, 0), pt) =
-                    cur.ux - a.dt * S / (rho_a * (1.0f + (a.nlA * kap_a) * pbar));
-#pragma unroll
-                for (int nu = 0; nu < L; ++nu)
-                    ntst(at_plane_w(plane_base(psi + (int64_t)nu * g.stride, g, 0), pt), cur.m[0][nu]);
-            }
-            // v_y at (i, j + 1/2)
-            if (j < ny - 1) {
-                const int sys = max(max(a.nb[1] - j, j - (ny - 2 - a.nb[1])), 0);
-                const Wts W = weights<PP>(
-                    a, PP ? 0.5f * (s0 + cell_r2(a, sr[(j + 1) % 3][t], sk[(j + 1) % 3][t])) : 0.0f);
-                float D = W.g0 * (w[4] - w[3]);
-                D = fmaf(W.g1, w[5] - w[2], D);
-                D = fmaf(W.g2, w[6] - w[1], D);
-                D = fmaf(W.g3, w[7] - w[0], D);
-                D = fmaf(W.g11, (rp[t + 5] - r0[t + 5]) + (rp[t + 3] - r0[t + 3]), D);
-                const int tt = sys * a.n_labels + cur.l;
-                const float2 *__restrict__ bc = a.bc1[1] + (int64_t)tt * L;
-                float S = a.w1[1][tt] * D;
-#pragma unroll
-                for (int nu = 0; nu < L; ++nu) {
-                    const float2 q = bc[nu];
-                    const float mn = fmaf(q.x, cur.m[1][nu], q.y * D);
-                    S += CENTRED ? cur.m[1][nu] : mn;
-                    cur.m[1][nu] = mn;
-                }
-                const float pbar = 0.5f * (w[3] + w[4]);
-                const float rho_a = 0.5f * (rr0[t] + sr[(j + 1) % 3][t]);
-                const float kap_a = 0.5f * (kk0[t] + sk[(j + 1) % 3][t]);
-                *at_plane_w(plane_base(vy, g, 0), pt) =
-                    cur.uy - a.dt * S / (rho_a * (1.0f + (a.nlA * kap_a) * pbar));
-#pragma unroll
-                for (int nu = 0; nu < L; ++nu)
-                    ntst(at_plane_w(plane_base(psi + (int64_t)(L + nu) * g.stride, g, 0), pt), cur.m[1][nu]);
-            }
-        }
-        if (PF) cur = nxt;
-    }
-}
-
-template <int L, bool CENTRED, int BX, bool PF, bool PP>
-__global__ void __launch_bounds__(BX) pressure_sweep2d(const StepArgs a, int rows, int nbx, int nblocks)
-{
-    __shared__ float sx[4][BX + 8];     // v_x rows, column c <-> x0 - 4 + c
-    __shared__ float sy[3][BX + 2];     // v_y rows, column c <-> x0 - 1 + c
-    const int tile = tile_of_block(blockIdx.x, nblocks);
-    pressure_tile2d<L, CENTRED, BX, PF, PP>(a, rows, (tile % nbx) * BX, (tile / nbx) * rows, sx, sy);
-}
-
 // Padded element offset of a flat unpadded index x + nx (y + ny z).
 __device__ __forceinline__ int64_t padded_index(const Geometry &g, int64_t f)
 {
@@ -581,23 +273,6 @@ __device__ __forceinline__ void record_receivers(const SparseArgs &s)
             s.trace[step * s.n + r] = s.p[padded_index(s.geo, s.idx[r])];
     __syncthreads();
     if (threadIdx.x == 0) s.step[0] = step + 1;
-}
-
-template <int L, bool CENTRED, int BX, bool PF, bool PP>
-__global__ void __launch_bounds__(BX) velocity_sweep2d(const StepArgs a, int rows, int nbx, int nblocks)
-{
-    // with receivers, block 0 records them (dispatched first, it overlaps the
-    // tiles instead of trailing them) and blocks 1.. take the tiles
-    const int shift = a.rcv.step ? 1 : 0;
-    if ((int)blockIdx.x < shift) {
-        record_receivers(a.rcv);
-        return;
-    }
-    __shared__ float sp[4][BX + 8];     // p rows, column c <-> x0 - 4 + c
-    __shared__ float sr[3][BX + 1];     // rho rows, column c <-> x0 + c
-    __shared__ float sk[3][BX + 1];     // kappa0 rows
-    const int tile = tile_of_block((int)blockIdx.x - shift, nblocks);
-    velocity_tile2d<L, CENTRED, BX, PF, PP>(a, rows, (tile % nbx) * BX, (tile / nbx) * rows, sp, sr, sk);
 }
 
 // ---------------------------------------------------------------------------
@@ -1011,29 +686,6 @@ __global__ void __launch_bounds__(BX *BY) velocity_sweep3d(const StepArgs a, int
     }
 }
 
-template <int L, bool C, bool PF, bool PP>
-hipError_t launch_sweep(const StepArgs &a, bool pressure, const KernelConfig &kc, hipStream_t st)
-{
-    const int nbx = (a.geo.n[0] + kc.bx - 1) / kc.bx;
-    const int nby = (a.geo.n[1] + kc.rows - 1) / kc.rows;
-    const int nblocks = nbx * nby;
-#define FW2_SWEEP(BXV)                                                                                  \
-    if constexpr (L <= 4 || BXV == 256)                                                                 \
-    if (kc.bx == BXV) {                                                                                 \
-        if (pressure)                                                                                   \
-            hipLaunchKernelGGL((pressure_sweep2d<L, C, BXV, PF, PP>), dim3(nblocks), dim3(BXV), 0, st, a, kc.rows, nbx, nblocks); \
-        else                                                                                            \
-            hipLaunchKernelGGL((velocity_sweep2d<L, C, BXV, PF, PP>), dim3(nblocks + (a.rcv.step ? 1 : 0)), dim3(BXV), 0, st, \
-                               a, kc.rows, nbx, nblocks);                                                  \
-        return hipGetLastError();                                                                       \
-    }
-    FW2_SWEEP(64)
-    FW2_SWEEP(128)
-    FW2_SWEEP(256)
-#undef FW2_SWEEP
-    return hipErrorInvalidValue;
-}
-
 template <int L, bool C, bool PP, int PF>
 hipError_t launch_sweep3(const StepArgs &a, bool pressure, const KernelConfig &kc, hipStream_t st)
 {
@@ -1063,95 +715,6 @@ hipError_t launch_sweep3(const StepArgs &a, bool pressure, const KernelConfig &k
     return hipErrorInvalidValue;
 }
 
-// ---------------------------------------------------------------------------
-// Batched 2D step: the same per-tile code as the single-domain sweeps, over
-// the tiles of every entry of a device table.
-// ---------------------------------------------------------------------------
-
-__device__ __forceinline__ int batch_entry_of_tile(const BatchTable *__restrict__ T, int t)
-{
-    int d = 0;
-    for (int k = 1; k < T->n; ++k)
-        if (T->e[k].tile_base <= t) d = k;
-    return d;
-}
-
-// One tile of one batch entry with the single-domain sweep's per-tile code.
-template <bool PRESSURE, int BX, int L, bool C, bool PP>
-__device__ __forceinline__ void batch_tile(const StepArgs &sa, int rows, int x0, int y0, float (*r0)[BX + 8],
-                                           float (*r1)[BX + 2], float (*r2)[BX + 1])
-{
-    if (PRESSURE)
-        pressure_tile2d<L, C, BX, false, PP>(sa, rows, x0, y0, r0, r1);
-    else
-        velocity_tile2d<L, C, BX, false, PP>(sa, rows, x0, y0, r0, r2, reinterpret_cast<float(*)[BX + 1]>(&r1[0][0]));
-}
-
-// Mechanism counts L0 .. L0 + 3 and both memory-variable schemes:
-// key = (L - L0) * 2 + scheme.
-template <bool PRESSURE, int BX, int L0, bool PP>
-__device__ __forceinline__ void batch_dispatch(int key, const StepArgs &sa, int rows, int x0, int y0,
-                                               float (*r0)[BX + 8], float (*r1)[BX + 2], float (*r2)[BX + 1])
-{
-    switch (key) {
-#define FW2_BCASE(K, DL, C) \
-    case K: batch_tile<PRESSURE, BX, L0 + DL, C, PP>(sa, rows, x0, y0, r0, r1, r2); break;
-    FW2_BCASE(0, 0, false) FW2_BCASE(1, 0, true) FW2_BCASE(2, 1, false) FW2_BCASE(3, 1, true)
-    FW2_BCASE(4, 2, false) FW2_BCASE(5, 2, true) FW2_BCASE(6, 3, false) FW2_BCASE(7, 3, true)
-#undef FW2_BCASE
-    default: break;
-    }
-}
-
-// One phase of the entries of one class of the table: CLASS bit 0 set for
-// 5..8 mechanisms (else 1..4), bit 1 set for per-point stencil weights.
-// Each class present gets a launch of its own, so that the larger register
-// demand of many mechanisms or per-point weights does not lower the
-// occupancy of the common class; entries are grouped by class, and each
-// launch walks only its class's range of the tile list.
-template <bool PRESSURE, int BX, int CLASS>
-__global__ void __launch_bounds__(BX) batch_phase(const BatchTable *__restrict__ T)
-{
-    constexpr bool MANY = (CLASS & 1) != 0, PP = (CLASS & 2) != 0;
-    __shared__ float r0[4][BX + 8];
-    __shared__ float r1[3][BX + 2];
-    __shared__ float r2[3][BX + 1];
-    // the class's own tiles: entries are grouped by class, so they are one
-    // contiguous range of the tile list
-    const int begin = T->class_begin[CLASS], total = T->class_end[CLASS] - begin, rows = T->rows;
-    // Blocks are dealt to the 8 XCDs round-robin; with a grid that is a
-    // multiple of 8, the blocks of XCD x walk one contiguous eighth of the
-    // range, so neighbouring tiles (which share halo rows) meet in the same L2.
-    int t = blockIdx.x, t_end = total, t_step = gridDim.x;
-    if (gridDim.x % 8 == 0) {
-        const int x = blockIdx.x % 8, q = total / 8, rem = total % 8;
-        const int start = x * q + min(x, rem);
-        t = start + blockIdx.x / 8;
-        t_end = start + q + (x < rem ? 1 : 0);
-        t_step = gridDim.x / 8;
-    }
-    for (; t < t_end; t += t_step) {
-        const int tile = begin + t;
-        const int d = batch_entry_of_tile(T, tile);
-        const BatchEntry &e = T->e[d];
-        if (batch_class(e.L, e.a.local_stencil) != CLASS) continue;     // (never: the range is the class's)
-        const long long step = *e.rcv.step;
-        // pressure phase of step s runs while the counter reads s; velocity after it moved to s + 1
-        const bool active = PRESSURE ? step < e.n_steps : (step >= 1 && step <= e.n_steps);
-        if (!active) continue;                      // uniform over the block
-        // the entry's arguments are read in place: the address is uniform
-        // over the block, so they load into scalar registers as a kernel's
-        // own arguments do
-        const StepArgs &sa = e.a;
-        const int nbx = (sa.geo.n[0] + BX - 1) / BX;
-        const int lt = tile - e.tile_base;
-        const int x0 = (lt % nbx) * BX, y0 = (lt / nbx) * rows;
-        const int key = (e.L - (MANY ? 5 : 1)) * 2 + e.scheme;
-        batch_dispatch<PRESSURE, BX, MANY ? 5 : 1, PP>(key, sa, rows, x0, y0, r0, r1, r2);
-        __syncthreads();                            // the LDS rings are reused by the next tile
-    }
-}
-
 template <int NDIM, int L, bool C, bool PP>
 hipError_t launch_p(const StepArgs &a, hipStream_t st)
 {
@@ -1173,22 +736,19 @@ hipError_t launch_v(const StepArgs &a, hipStream_t st)
 template <bool P, int NDIM, int L, bool C, bool PP>
 hipError_t dispatch_variant(const StepArgs &a, const KernelConfig &kc, hipStream_t st)
 {
-    if constexpr (L > 4) {
-        // more than four mechanisms: the generic kernel, or one sweep shape per
-        // dimension (256-column 2D rows; 64 x 8 3D columns without the plane
-        // prefetch, whose second copy of the memory variables would not fit
-        // the registers)
-        if (kc.variant == 0) return P ? launch_p<NDIM, L, C, PP>(a, st) : launch_v<NDIM, L, C, PP>(a, st);
-        if (NDIM == 2) return launch_sweep<L, C, false, PP>(a, P, KernelConfig{1, 256, kc.rows}, st);
-        return launch_sweep3<L, C, PP, 0>(a, P, KernelConfig{1, 64, kc.rows}, st);
-    } else {
-        if (NDIM == 3 && kc.variant == 1) return launch_sweep3<L, C, PP, 0>(a, P, kc, st);
-        if (NDIM == 3 && kc.variant == 2) return launch_sweep3<L, C, PP, 1>(a, P, kc, st);
-        if (NDIM == 3 && kc.variant == 3) return launch_sweep3<L, C, PP, 2>(a, P, kc, st);
-        if (NDIM == 2 && kc.variant == 1) return launch_sweep<L, C, false, PP>(a, P, kc, st);
-        if (NDIM == 2 && kc.variant == 2) return launch_sweep<L, C, true, PP>(a, P, kc, st);
-        return P ? launch_p<NDIM, L, C, PP>(a, st) : launch_v<NDIM, L, C, PP>(a, st);
+    if constexpr (NDIM == 3) {
+        if constexpr (L > 4) {
+            // more than four mechanisms: one sweep shape (64 x 8 columns without
+            // the plane prefetch, whose second copy of the memory variables
+            // would not fit the registers)
+            if (kc.variant != 0) return launch_sweep3<L, C, PP, 0>(a, P, KernelConfig{1, 64, kc.rows}, st);
+        } else {
+            if (kc.variant == 1) return launch_sweep3<L, C, PP, 0>(a, P, kc, st);
+            if (kc.variant == 2) return launch_sweep3<L, C, PP, 1>(a, P, kc, st);
+            if (kc.variant == 3) return launch_sweep3<L, C, PP, 2>(a, P, kc, st);
+        }
     }
+    return P ? launch_p<NDIM, L, C, PP>(a, st) : launch_v<NDIM, L, C, PP>(a, st);
 }
 
 template <bool P, int NDIM, int L>

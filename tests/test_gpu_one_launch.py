@@ -56,7 +56,7 @@ SHAPES = [(64, 16), (65, 17), (63, 49), (128, 24), (200, 77), (5, 3), (1, 9), (1
 def test_one_launch_steps_equal_two_phases(shape, L, scheme, local, monkeypatch):
     prob = _problem(shape, L, scheme, local, n_src=min(40, shape[0] * shape[1]))
     state = W.random_state(2, L, shape, seed=L)
-    ref, at = _run(prob, "1,256,4", monkeypatch, 4, (7, 1, 4), state)
+    ref, at = _run(prob, "0,64,8", monkeypatch, 4, (7, 1, 4), state)
     for config in ("4,64,8", "4,64,12", "4,64,16", None):
         for chunk in (4, 3, 0):                     # graphs of even and odd length, direct launches
             got, at2 = _run(prob, config, monkeypatch, chunk, (7, 1, 4), state)
@@ -71,7 +71,7 @@ def test_source_counts_at_the_one_launch_limit(n_src, monkeypatch):
     shape = (140, 90)
     prob = _problem(shape, 2, 1, 0, n_src)
     state = W.random_state(2, 2, shape, seed=8)
-    ref, _ = _run(prob, "1,256,4", monkeypatch, 4, (9,), state)
+    ref, _ = _run(prob, "0,64,8", monkeypatch, 4, (9,), state)
     got, _ = _run(prob, None, monkeypatch, 4, (9,), state)
     for k in ref:
         assert np.array_equal(ref[k], got[k]), k
@@ -81,7 +81,7 @@ def test_removing_and_adding_sources_and_receivers(monkeypatch):
     """Captured one-launch graphs follow a change of sources and receivers."""
     prob = _problem((90, 70), 2, 1, 0, 30)
     outs = []
-    for config in ("1,256,4", None):
+    for config in ("0,64,8", None):
         if config is None:
             monkeypatch.delenv("FW2_KERNEL_CONFIG", raising=False)
         else:
