@@ -297,8 +297,16 @@ constexpr int64_t kScanPairs = (int64_t)4 << 20;
 bool phase_adds_sources(const fw2_domain *d)
 {
     const fw2::Geometry &g = d->ly.geo;
-    const int64_t tiles = (int64_t)((g.n[0] + 63) / 64) * ((g.n[1] + 7) / 8);
-    return d->kc.variant == 5 && d->src.n <= fw2::kTileSources && tiles * d->src.n <= kScanPairs;
+    const fw2::KernelConfig &kc = d->kc;
+    if (kc.variant == 0) return false;
+    if (g.ndim == 2) {
+        const int64_t tiles = (int64_t)((g.n[0] + 63) / 64) * ((g.n[1] + 7) / 8);
+        return d->src.n <= fw2::kTileSources && tiles * d->src.n <= kScanPairs;
+    }
+    // 3D: blocks of one column tile by kc.rows planes (16 x 8 the least tile)
+    const int by = kc.by ? kc.by : (kc.bx == 64 ? 8 : 16), bx = d->desc.n_relax > 4 ? 64 : kc.bx;
+    const int64_t tiles = (int64_t)((g.n[0] + bx - 1) / bx) * ((g.n[1] + by - 1) / by) * ((g.n[2] + kc.rows - 1) / kc.rows);
+    return d->src.n <= fw2::kTileSources3 && tiles * d->src.n <= kScanPairs;
 }
 
 void sync_sparse_args(fw2_domain *d)

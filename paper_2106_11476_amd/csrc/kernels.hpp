@@ -95,7 +95,8 @@ struct StepArgs {
 // (64 x 8) tile, every stencil tap a cached global load (any ndim).
 // 3D: variant 1, plane sweeps of a column tile (32x16, 64x8 or 16x16 for bx =
 // 32, 64, 16) over `rows` planes with a register window along z and LDS plane
-// rings; variant 2, the same with every load of the next plane issued during
+// rings (each of the three adds the sources in a.src in its pressure phase);
+// variant 2, the same with every load of the next plane issued during
 // the current one; variant 3, only the staged planes and the z window one
 // plane ahead, the point's own values at the top of their plane.
 // 2D: variant 4 (at most four mechanisms), a whole step out of place in one
@@ -118,6 +119,8 @@ constexpr int kMaxBatch = 64;
 // The most sources the tiles of a 2D kernel add themselves (each reads the
 // list); more are added by a launch of their own.
 constexpr int32_t kTileSources = 4096;
+// The same for the 3D sweeps, which list a tile's sources in LDS.
+constexpr int32_t kTileSources3 = 1024;
 
 struct BatchEntry {
     StepArgs a;

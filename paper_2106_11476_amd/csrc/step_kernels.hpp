@@ -339,6 +339,41 @@ __device__ __forceinline__ void stage_store(float *dst, const Staged<W, H, NT> &
     }
 }
 
+// The sources of a block's tile (BX x BY columns from (x0, y0), planes z0 ..
+// zend - 1), listed when the block starts, where the reads of the source list
+// overlap the prologue's loads, and added once its pressures are stored.
+// Blocks without a source (nearly all) only read the list.
+struct TileSources {
+    int n;
+    int at[kTileSources3];
+};
+
+template <int BX, int BY>
+__device__ __forceinline__ void list_sources(TileSources &t, const SparseArgs &s, const Geometry &g, int x0, int y0,
+                                             int z0, int zend, int tid)
+{
+    if (tid == 0) t.n = 0;
+    __syncthreads();
+    const int64_t nxy = (int64_t)g.n[0] * g.n[1], lo = z0 * nxy, hi = zend * nxy;
+    for (int q = tid; q < s.n; q += BX * BY) {
+        const int64_t f = s.idx[q];
+        if (f < lo || f >= hi) continue;
+        const uint32_t r = (uint32_t)(f % nxy), y = r / (uint32_t)g.n[0], x = r - y * (uint32_t)g.n[0];
+        if (x - (uint32_t)x0 < (uint32_t)BX && y - (uint32_t)y0 < (uint32_t)BY) t.at[atomicAdd(&t.n, 1)] = q;
+    }
+}
+
+template <int NT>
+__device__ __forceinline__ void add_sources(const TileSources &t, const SparseArgs &s, float *p, long long step, int tid)
+{
+    __syncthreads();                                 // the block's pressures are stored
+    for (int k = tid; k < t.n; k += NT) {
+        const int q = t.at[k];
+        const int64_t pi = padded_index(s.geo, s.idx[q]);
+        p[pi] = p[pi] + s.w[q] * s.signals[(int64_t)s.sig[q] * s.n_t + step];
+    }
+}
+
 // PF: 0 -- every plane's loads issued in its own iteration; 1 -- all loads
 // of plane k + 1 issued during plane k; 2 -- only the staged planes and the
 // z window one plane ahead, the point's own values (medium, memory
@@ -367,6 +402,7 @@ __global__ void __launch_bounds__(BX *BY) pressure_sweep3d(const StepArgs a, int
     __shared__ float sx[4][XH * XW];
     __shared__ float sy[4][YH * YW];
     __shared__ float sz[3][ZH * ZW];
+    __shared__ TileSources srcs;
 
     float w[8];
     w[0] = 0.0f;
@@ -382,6 +418,13 @@ __global__ void __launch_bounds__(BX *BY) pressure_sweep3d(const StepArgs a, int
     const int s0 = max(max(a.nb[0] - i, i - (nx - 1 - a.nb[0])), 0);
     const int s1 = max(max(a.nb[1] - j, j - (ny - 1 - a.nb[1])), 0);
     const int zend = min(z0 + rows, nz);
+    long long step = 0;
+    bool sources = false;
+    if (a.src.n > 0) {
+        step = *a.src.step;
+        sources = step < a.src.n_t;
+        if (sources) list_sources<BX, BY>(srcs, a.src, g, x0, y0, z0, zend, tid);
+    }
     // what one plane k needs from global memory besides the staged planes
     struct Own {
         float vzn, p0, k0, q0, r0;
@@ -510,6 +553,7 @@ __global__ void __launch_bounds__(BX *BY) pressure_sweep3d(const StepArgs a, int
                     ntst(at_plane_w(plane_base(a.psi2 + a.out + (int64_t)(ax * L + nu) * g.stride, g, k), pt), m[ax][nu]);
         }
     }
+    if (sources) add_sources<NT>(srcs, a.src, a.p + a.out, step, tid);
 }
 
 template <int L, bool CENTRED, int BX, int BY, bool PP, int PF>

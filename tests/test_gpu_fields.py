@@ -71,3 +71,26 @@ def test_3d_tile_and_march_choice_does_not_change_results(n, L, monkeypatch):
     for k in got[0][0]:
         assert np.array_equal(got[0][0][k], got[1][0][k]), k
     assert np.array_equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("shape,L", [((70, 21, 30), 2), ((40, 33, 17), 3), ((66, 9, 40), 6)])
+def test_3d_sources_added_by_the_sweeps_equal_a_launch_of_their_own(shape, L):
+    """Up to 1024 sources are added by the pressure sweep; one more source, of
+    weight zero, makes the same sources take a launch of their own."""
+    rng = np.random.default_rng(L)
+    prob = W.random_medium(shape, L, 2, seed=4, nb=3, ntr=2)
+    idx = rng.choice(prob.npts, 1025, replace=False).astype(np.int64)
+    prob.signals = (1e4 * rng.standard_normal((2, 5))).astype(np.float32)    # ends within the run
+    prob.rcv_idx = idx[:7]
+    got = []
+    for n in (1024, 1025):
+        prob.src_idx, prob.src_sig = idx[:n], (np.arange(n) % 2).astype(np.int32)
+        prob.src_w = np.append(rng.uniform(0.5, 1.0, 1024) if not got else got[0][2][:1024],
+                               [0.0])[:n].astype(np.float32)
+        dom = fw2.from_problem(prob, device="cuda:0", cap_steps=7)
+        dom.step(7)
+        got.append((dom.read_fields(fw2.FIELD_ALL), dom.trace.cpu().numpy(), prob.src_w))
+        dom.destroy_domain()
+    for k in got[0][0]:
+        assert np.array_equal(got[0][0][k], got[1][0][k]), k
+    assert np.array_equal(got[0][1], got[1][1]) and np.any(got[0][1])
