@@ -782,10 +782,12 @@ hipError_t dispatch_variant(const StepArgs &a, const KernelConfig &kc, hipStream
 {
     if constexpr (NDIM == 3) {
         if constexpr (L > 4) {
-            // more than four mechanisms: one sweep shape (64 x 8 columns without
-            // the plane prefetch, whose second copy of the memory variables
-            // would not fit the registers)
-            if (kc.variant != 0) return launch_sweep3<L, C, PP, 0>(a, P, KernelConfig{1, 64, kc.rows}, st);
+            // more than four mechanisms: one sweep shape, 64 x 8 columns with the
+            // staged planes one ahead (us per step against no prefetch: 400 x
+            // 300 x 300, L = 5 2393 / 2763; 200^3, L = 6 614 / 683; 300^3,
+            // L = 8 2692 / 2818; a copy of the memory variables one plane
+            // ahead would not fit the registers)
+            if (kc.variant != 0) return launch_sweep3<L, C, PP, 2>(a, P, KernelConfig{3, 64, kc.rows}, st);
         } else {
             if (kc.variant == 1) return launch_sweep3<L, C, PP, 0>(a, P, kc, st);
             if (kc.variant == 2) return launch_sweep3<L, C, PP, 1>(a, P, kc, st);
