@@ -1,12 +1,13 @@
 // Batched 2D step of many domains (continuous batching): two launches a step
 // over the LDS tiles (tile2d.hpp) of every active entry of a device table.
 //
-// 32 domains of 128..384 points a side (2.3 M points, L = 2..4): 78.7 us a step
+// 32 domains of 128..384 points a side (2.3 M points, L = 2..4): 71.2 us a step
 // where 256-column row sweeps with a launch for the sources took 113.  What
 // that took: tiles of 64 columns (few idle lanes on narrow grids), the entry
 // found by a ballot, the entry's arguments in scalar registers and its tables
-// by global (not flat) loads, registers for four blocks a CU (85 -> 60), and
-// no launch between the phases.  8 domains (0.36 M points): 19.0 against 26.6.
+// by global (not flat) loads, registers for four blocks a CU (85 -> 60), no
+// launch between the phases, and memory variables that stay in the cache (the
+// last: 78.7 -> 71.2).  8 domains (0.36 M points): 16.7 against 26.6.
 #include "tile2d.hpp"
 
 #include <mutex>

@@ -114,32 +114,37 @@ fw2_status validate_scalars(const fw2_domain_desc *d)
     return FW2_OK;
 }
 
-// 2D grids advanced by one launch a step, out of place (step_f2.hip): their
-// workspace holds a second state block.  The two state blocks and the medium
-// have to stay in the 256 MiB last-level cache (the bound leaves a little over,
-// as not all of it is touched at once).  Measured, us per step, two phases
-// against one launch: 128^2, L = 2 13.6 / 5.0; 480^2, L = 2 17.1 / 8.0;
-// 1024^2, L = 3 37.7 / 31.2; 1300 x 1200, L = 4 67.2 / 49.4; 1600^2, L = 2
-// (255 MiB) 64.8 / 54.7; 2000^2, L = 1 (269 MiB) 72.8 / 74.0; past it 1700^2,
-// L = 2 (283 MiB) 70.2 / 79.3, 1400^2, L = 4 (325 MiB) 74.1 / 86.8.
-constexpr int64_t kOneLaunchBytes = (int64_t)264 << 20;
+// Arrays of a step up to this size stay in the 256 MiB last-level cache from
+// one step to the next.  Up to it the two-phase 2D tiles (all entries of a
+// batch together) read and write the memory variables by plain accesses, past
+// it by non-temporal ones, which leave the cache to the arrays that both
+// phases read.  Measured, us per step, plain / non-temporal: 1237 x 893, L = 8
+// (175 MB) 59.1 / 69.2; 1600^2, L = 4 (235 MB) 74.6 / 82.0; 2400 x 2300, L = 1
+// (249 MB) 81.1 / 92.0; 1700^2, L = 4 (261 MB) 100 / 95.6; 2000 x 1900, L = 3
+// (277 MB) 107 / 99.5; 4096 x 2048, L = 4 303 / 242.  The 3D sweeps keep the
+// hint: plain accesses gain 7% at 126^3 and lose from 140^3 on.
+constexpr int64_t kCacheBytes = (int64_t)240 << 20;
 
+// 2D grids advanced by one launch a step, out of place (step_f2.hip; their
+// workspace holds a second state block): those whose two state blocks and
+// medium stay in the cache, and with more than two mechanisms only while every
+// 64 x 16 tile has a CU of its own.  Measured, us per step, two phases against
+// one launch: L = 2 128^2 6.4 / 5.0, 480^2 9.4 / 8.0, 1024^2 25.9 / 23.4,
+// 1536^2 (240 MB) 50.2 / 45.7, 1600^2 (267 MB) 53.7 / 55.0; L = 4 480^2 11.4 /
+// 10.6; L = 3 600 x 500 12.5 / 12.4, 1024^2 31.0 / 31.1.
 bool one_launch_size(const fw2_domain_desc *d, int64_t stride)
 {
     const int n_state = 1 + d->ndim + 2 * d->ndim * d->n_relax;
-    return d->ndim == 2 && d->n_relax <= 4 && (2 * n_state + 3) * stride * 4 <= kOneLaunchBytes;
+    if (d->ndim != 2 || d->n_relax > 4 || (2 * n_state + 3) * stride * 4 > kCacheBytes) return false;
+    return d->n_relax <= 2 || (d->n[0] + 63) / 64 * ((d->n[1] + 15) / 16) <= 256;
 }
 
 // Tile rows of the one-launch step: the smallest tiles (shortest load latency)
-// while every tile has a CU of its own, then 16 rows while those do, then the
-// tile whose registers let two blocks share a CU (480^2, L = 2: 16 rows 8.0 us
-// a step, 8 rows 8.7; 600 x 500, L = 3: 12 rows 12.3, 16 rows 14.9, 8 rows
-// 14.9; 1024^2, L = 2: 16 rows 23.1, 12 rows 25.4).
-int one_launch_rows(const fw2::Geometry &g, int L)
+// while every tile has a CU of its own, else 16 (480^2, L = 2: 16 rows 8.0 us
+// a step, 8 rows 8.7; 1024^2, L = 2 23.4 / 27.9).
+int one_launch_rows(const fw2::Geometry &g)
 {
-    const int64_t cols = (g.n[0] + 63) / 64;
-    if (cols * ((g.n[1] + 7) / 8) <= 256) return 8;
-    return L <= 2 || cols * ((g.n[1] + 15) / 16) <= 256 ? 16 : 12;
+    return (int64_t)((g.n[0] + 63) / 64) * ((g.n[1] + 7) / 8) <= 256 ? 8 : 16;
 }
 
 void make_layout(const fw2_domain_desc *d, Layout *ly)
@@ -639,6 +644,7 @@ fw2_status fw2_create_domain(const fw2_domain_desc *desc, void *dev_workspace, u
     a.rho = rho;
     a.label = ly.label_off ? d->ws + ly.label_off : nullptr;
     a.n_labels = desc->n_labels;
+    a.stream = (int64_t)(1 + nd + 2 * nd * L + 3) * g.stride * 4 > kCacheBytes;
     double nlA, nlB0, nlB1;
     nl_coefficients(desc, &nlA, &nlB0, &nlB1);
     a.nlA = (float)nlA;
@@ -790,13 +796,13 @@ fw2_status fw2_create_domain(const fw2_domain_desc *desc, void *dev_workspace, u
     }
 
     d->kc = nd == 2 ? fw2::KernelConfig{5, 64, 8} : sweep3d_config(g, L);
-    if (ly.shadow) d->one = fw2::KernelConfig{4, 64, one_launch_rows(g, L)};
+    if (ly.shadow) d->one = fw2::KernelConfig{4, 64, one_launch_rows(g)};
     if (const char *ev = std::getenv("FW2_KERNEL_CONFIG")) {      // "variant,bx,rows[,by]" (tuning runs)
         int v = 0, bx = 0, ry = 0, by = 0;
         const int nparsed = std::sscanf(ev, "%d,%d,%d,%d", &v, &bx, &ry, &by);
         const bool parsed = nparsed == 3 || nparsed == 4;
         const bool ok2 = nd == 2 && by == 0 && (v == 0 || (v == 5 && (ry == 8 || ry == 16))) && (bx == 64 || bx == 128 || bx == 256);
-        if (parsed && v == 4 && by == 0 && ly.shadow && (ry == 8 || ry == 12 || ry == 16)) d->one = fw2::KernelConfig{4, bx, ry};
+        if (parsed && v == 4 && by == 0 && ly.shadow && (ry == 8 || ry == 16)) d->one = fw2::KernelConfig{4, bx, ry};
         const bool tile3 = by == 0 ? (bx == 16 || bx == 32 || bx == 64)
                                    : (v == 3 && ((bx == 64 && by == 4) || (bx == 32 && by == 8)));
         const bool ok3 = nd == 3 && (v == 0 || ((v >= 1 && v <= 3) && tile3));
@@ -1433,14 +1439,17 @@ fw2_status fw2_batch_set_domains(fw2_batch *b, int32_t n, fw2_domain *const *dom
     T.rows = b->rows;
     int tiles = 0, m = 0;
     bool sources = false;
+    int64_t bytes = 0;
     for (int32_t k = 0; k < n; ++k) {
         fw2_domain *d = domains[k];
+        bytes += (state_floats(d) + 3 * d->ly.geo.stride) * 4;
         sources |= d->src.n > fw2::kTileSources;
         // the domain's own queued work must be finished before the batch stream touches it
         FW2_HIP(hipStreamSynchronize(d->stream));
         b->doms.push_back(d);
         b->target.push_back(n_steps[k]);
     }
+    const int32_t stream = bytes > kCacheBytes;     // the entries share the cache
     // entries grouped by launch class, so that each class launch walks only
     // its own tiles, spread over every XCD
     for (int c = 0; c < 4; ++c) {
@@ -1449,6 +1458,7 @@ fw2_status fw2_batch_set_domains(fw2_batch *b, int32_t n, fw2_domain *const *dom
             fw2_domain *d = domains[k];
             if (fw2::batch_class(d->desc.n_relax, d->args.local_stencil) != c) continue;
             T.e[m].a = d->args;
+            T.e[m].a.stream = stream;
             T.e[m].a.src = d->src;
             T.e[m].rcv = d->rcv;
             const int ty = tile_rows(b);

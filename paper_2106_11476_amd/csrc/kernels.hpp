@@ -18,9 +18,11 @@ namespace fw2 {
 
 constexpr int kHalo = 4;
 
-// Memory variables are read and written once per step, by one kernel:
-// non-temporal accesses keep them from displacing the stencil fields that
-// the other kernel of the step reads back from cache.
+// Memory variables are read and written once per step, by one kernel.  Where
+// the arrays of a step exceed the last-level cache, non-temporal accesses keep
+// them from displacing the stencil fields that the other kernel of the step
+// reads back; where they fit, plain ones leave them there for the next step
+// (2D tiles, StepArgs::stream).
 __device__ __forceinline__ float ntld(const float *p) { return __builtin_nontemporal_load(p); }
 __device__ __forceinline__ void ntst(float *p, float v) { __builtin_nontemporal_store(v, p); }
 
@@ -61,6 +63,7 @@ struct StepArgs {
     const float *rho;        // rho0
     const uint8_t *label;    // nullptr: a single relaxation tuple
     int32_t n_labels;
+    int32_t stream;          // 2D tiles: memory variables by non-temporal accesses
     int32_t nb[3];           // boundary cells per axis
     const float *w2[3];      // pressure-point tables per axis: [slot][label]
     const float2 *bc2[3];    //   [slot][label][nu] (b, c)

@@ -12,9 +12,10 @@
 // Per-point arithmetic is that of the two-phase sweeps (bitwise equal results).
 //
 // Bound by the load latency and the hand-over while every tile has a CU of its
-// own (128^2, L = 2: 5.0 us a step, 13.6 with two phases and a source launch;
-// 480^2: 8.0 against 17.1), by the cache's bandwidth above (1536^2, L = 2:
-// 46.1 against 60.2 us; a tile of 64 x 16 reads 1.6 times its cells).
+// own (128^2, L = 2: 5.0 us a step; 480^2: 8.0), by the cache's bandwidth above
+// (1536^2, L = 2: 45.7 us; a tile of 64 x 16 reads 1.6 times its cells, so the
+// memory variables go through the caches plainly: with the non-temporal hint
+// 1536^2 takes 63.4).
 #include "step_kernels.hpp"
 
 namespace fw2 {
@@ -287,17 +288,15 @@ hipError_t launch_tiles(const StepArgs &a, hipStream_t st)
     return hipGetLastError();
 }
 
-// Tile rows 8, 12 or 16 (one_launch_rows in fw2.cpp picks them).  NT covers a
-// tile's pressure cells in two passes and, 8 rows apart, its velocity points
-// in one; WV asks for the registers that let two blocks share a CU where that
-// does not spill (62 registers at L <= 2 for 1024 threads, 70-78 at L = 3, 4
-// for 768).
+// Tile rows 8 or 16 (one_launch_rows in fw2.cpp picks them).  NT covers a
+// tile's pressure cells in two passes and its velocity points in one; WV asks
+// for the registers that let two blocks of 1024 threads share a CU where that
+// does not spill (62 registers at L <= 2; above, such grids take two phases).
 template <int L, bool C, bool PP>
 hipError_t launch_fused(const StepArgs &a, const KernelConfig &kc, hipStream_t st)
 {
     if (kc.rows == 8) return launch_tiles<L, C, PP, 8, 576, 1>(a, st);
     if (kc.rows == 16) return launch_tiles<L, C, PP, 16, 1024, L <= 2 ? 8 : 1>(a, st);
-    if (kc.rows == 12) return launch_tiles<L, C, PP, 12, 768, 6>(a, st);
     return hipErrorInvalidValue;
 }
 

@@ -3,14 +3,14 @@
 // A block issues every load of its tile at once (the stencil field's window
 // with its halo, the point's own values), so a tile costs one exposed load
 // latency, and stencil taps come from LDS.  Bound by HBM streaming on large
-// grids, by that latency on small ones.  They replace row sweeps (256 columns,
-// a register window along y, one exposed latency and one barrier a row); us
-// per step, sweeps against tiles of 8 rows: 128^2, L = 2 13.8 / 6.3; 1536^2,
-// L = 4 83.8 / 78.4; 2400 x 2300, L = 1 99.8 / 92.7; 1237 x 893, L = 8, per-
-// point weights 76.1 / 69.1; 4096 x 2048, L = 4 247 / 243 (6.3 TB/s of its
-// 182 B a point); 8192 x 4096, L = 2 886 / 749.  Tiles of 16 rows: 254 at
-// 4096 x 2048, L = 4, 762 at 8192 x 4096, 287 against 290-300 at 3072^2,
-// L = 3; of 4 rows 241, 787, 291.
+// grids, by the cache's bandwidth where the arrays stay there, by that latency
+// on small ones.  They replace row sweeps (256 columns, a register window along
+// y, one exposed latency and one barrier a row); us per step, sweeps against
+// tiles of 8 rows: 128^2, L = 2 13.8 / 6.4; 1536^2, L = 4 83.8 / 67.9; 2400 x
+// 2300, L = 1 99.8 / 84.0; 1237 x 893, L = 8, per-point weights 76.1 / 59.1;
+// 4096 x 2048, L = 4 247 / 235-243 (6.3 TB/s of its 182 B a point); 8192 x
+// 4096, L = 2 886 / 749.  Tiles of 16 rows: 254 at 4096 x 2048, L = 4, 762 at
+// 8192 x 4096, 287 against 290-300 at 3072^2, L = 3; of 4 rows 241, 787, 291.
 #pragma once
 
 #include "step_kernels.hpp"
@@ -47,6 +47,42 @@ struct Window {
             if (tid + q * NT < W * H) dst[tid + q * NT] = r[q];
     }
 };
+
+// The values at point pt of N consecutive arrays from f.  The empty
+// asm statements keep the compiler from merging the two branches, which would
+// drop the hint.
+#define FW2_BRANCH(name) asm volatile("; " name ::: "memory")
+template <int N>
+__device__ __forceinline__ void load_memory(float *m, const float *f, const Geometry &g, uint32_t pt, bool stream)
+{
+    if (stream) {
+        FW2_BRANCH("stream");
+#pragma unroll
+        for (int q = 0; q < N; ++q) m[q] = ntld(at_plane(plane_base(f + q * g.stride, g, 0), pt));
+        FW2_BRANCH("stream end");
+    } else {
+        FW2_BRANCH("cached");
+#pragma unroll
+        for (int q = 0; q < N; ++q) m[q] = *at_plane(plane_base(f + q * g.stride, g, 0), pt);
+        FW2_BRANCH("cached end");
+    }
+}
+template <int N>
+__device__ __forceinline__ void store_memory(const float *m, float *f, const Geometry &g, uint32_t pt, bool stream)
+{
+    if (stream) {
+        FW2_BRANCH("stream");
+#pragma unroll
+        for (int q = 0; q < N; ++q) ntst(at_plane_w(plane_base(f + q * g.stride, g, 0), pt), m[q]);
+        FW2_BRANCH("stream end");
+    } else {
+        FW2_BRANCH("cached");
+#pragma unroll
+        for (int q = 0; q < N; ++q) *at_plane_w(plane_base(f + q * g.stride, g, 0), pt) = m[q];
+        FW2_BRANCH("cached end");
+    }
+}
+#undef FW2_BRANCH
 
 // LDS of a pressure tile: v_x and v_y with the reach of D^- (4 cells before,
 // 3 after, 1 across) and the tile's sources; of a velocity tile: p with the
@@ -88,11 +124,7 @@ __device__ __forceinline__ void pressure_tile(const StepArgs &a, int x0, int y0,
         k0 = *at_plane(plane_base(a.kap, g, 0), pt);
         q0 = *at_plane(plane_base(a.nlq, g, 0), pt);
         if (PP) r0 = *at_plane(plane_base(a.rho, g, 0), pt);
-#pragma unroll
-        for (int ax = 0; ax < 2; ++ax)
-#pragma unroll
-            for (int nu = 0; nu < L; ++nu)
-                m[ax][nu] = ntld(at_plane(plane_base(a.psi2 + (int64_t)(ax * L + nu) * g.stride, g, 0), pt));
+        load_memory<2 * L>(&m[0][0], a.psi2, g, pt, a.stream);
     }
     if (n_src > 0) {                                 // the sources of the tile's cells
         lds.src[tid] = 0;
@@ -144,11 +176,7 @@ __device__ __forceinline__ void pressure_tile(const StepArgs &a, int x0, int y0,
         pn = fmaf(s.w[k], s.signals[(int64_t)s.sig[k] * s.n_t + step], pn);
     }
     *at_plane_w(plane_base(a.p + a.out, g, 0), pt) = pn;
-#pragma unroll
-    for (int ax = 0; ax < 2; ++ax)
-#pragma unroll
-        for (int nu = 0; nu < L; ++nu)
-            ntst(at_plane_w(plane_base(a.psi2 + a.out + (int64_t)(ax * L + nu) * g.stride, g, 0), pt), m[ax][nu]);
+    store_memory<2 * L>(&m[0][0], a.psi2 + a.out, g, pt, a.stream);
 }
 
 // Velocity phase of the tile at (x0, y0).
@@ -177,10 +205,8 @@ __device__ __forceinline__ void velocity_tile(const StepArgs &a, int x0, int y0,
             rn[ax] = *at_plane(br, nb);
             kn[ax] = *at_plane(bk, nb);
             u[ax] = *at_plane(plane_base(a.v + (int64_t)ax * g.stride, g, 0), pt);
-#pragma unroll
-            for (int nu = 0; nu < L; ++nu)
-                m[ax][nu] = ntld(at_plane(plane_base(a.psi1 + (int64_t)(ax * L + nu) * g.stride, g, 0), pt));
         }
+        load_memory<2 * L>(&m[0][0], a.psi1, g, pt, a.stream);
     }
     wp.store(lds.p, tid);
     __syncthreads();
@@ -218,9 +244,7 @@ __device__ __forceinline__ void velocity_tile(const StepArgs &a, int x0, int y0,
         const float kap_a = 0.5f * (k0 + kn[ax]);
         *at_plane_w(plane_base(a.v + a.out + (int64_t)ax * g.stride, g, 0), pt) =
             u[ax] - a.dt * S / (rho_a * (1.0f + (a.nlA * kap_a) * pbar));
-#pragma unroll
-        for (int nu = 0; nu < L; ++nu)
-            ntst(at_plane_w(plane_base(a.psi1 + a.out + (int64_t)(ax * L + nu) * g.stride, g, 0), pt), m[ax][nu]);
+        store_memory<L>(&m[ax][0], a.psi1 + a.out + (int64_t)(ax * L) * g.stride, g, pt, a.stream);
     }
 }
 

@@ -47,7 +47,7 @@ def _run(prob, config, monkeypatch, chunk, steps, state):
     return out, at
 
 
-# tile edges (64 columns; 8, 12 and 16 rows) and grids below the stencil's reach
+# tile edges (64 columns; 8 and 16 rows) and grids below the stencil's reach
 SHAPES = [(64, 16), (65, 17), (63, 49), (128, 24), (200, 77), (5, 3), (1, 9), (130, 1)]
 
 
@@ -57,7 +57,7 @@ def test_one_launch_steps_equal_two_phases(shape, L, scheme, local, monkeypatch)
     prob = _problem(shape, L, scheme, local, n_src=min(40, shape[0] * shape[1]))
     state = W.random_state(2, L, shape, seed=L)
     ref, at = _run(prob, "0,64,8", monkeypatch, 4, (7, 1, 4), state)
-    for config in ("4,64,8", "4,64,12", "4,64,16", None):
+    for config in ("4,64,8", "4,64,16", "5,64,8", None):
         for chunk in (4, 3, 0):                     # graphs of even and odd length, direct launches
             got, at2 = _run(prob, config, monkeypatch, chunk, (7, 1, 4), state)
             assert at2 == at == 12
@@ -98,3 +98,15 @@ def test_removing_and_adding_sources_and_receivers(monkeypatch):
         dom.destroy_domain()
     for a, b in zip(*outs):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("shape,L", [((1100, 900), 4), ((1900, 1700), 4), ((1030, 1000), 2)])
+def test_grids_around_the_cache_limits_equal_the_per_point_kernels(shape, L, monkeypatch):
+    """Two phases with the memory variables kept in the cache (217 MB of arrays
+    at most), streamed past it (300 MB), and one launch of many tiles."""
+    prob = _problem(shape, L, 1, 0, 5)
+    state = W.random_state(2, L, shape, seed=2)
+    ref, _ = _run(prob, "0,64,8", monkeypatch, 4, (3,), state)
+    got, _ = _run(prob, None, monkeypatch, 4, (3,), state)
+    for k in ref:
+        assert np.array_equal(ref[k], got[k]), k
