@@ -460,6 +460,25 @@ fw2_status copy_box(fw2_domain *d, float *dev_base, void *packed, bool to_device
     return FW2_OK;
 }
 
+// Whether a kernel can reach all of [buf, buf + bytes): memory of the current
+// device inside one allocation.  Any other buffer is left to the copy calls,
+// which serve it or return an error.
+bool device_range(const void *buf, uint64_t bytes)
+{
+    hipPointerAttribute_t at;
+    int dev = -1;
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipPointerGetAttributes(&at, buf) != hipSuccess ||
+        at.type != hipMemoryTypeDevice || at.device != dev ||
+        hipMemGetAddressRange(&base, &size, const_cast<void *>(buf)) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    const uint64_t off = (uint64_t)((const char *)buf - (const char *)base);
+    return off <= size && bytes <= size - off;
+}
+
 fw2_status transfer_fields(fw2_domain *d, uint32_t mask, void *buf, int32_t kind, bool to_device)
 {
     if (!d) return fail(FW2_E_STATE, "domain is NULL");
@@ -470,7 +489,10 @@ fw2_status transfer_fields(fw2_domain *d, uint32_t mask, void *buf, int32_t kind
                                                : (to_device ? hipMemcpyHostToDevice : hipMemcpyDeviceToHost);
     const fw2::Geometry &g = d->ly.geo;
     const int nd = g.ndim, L = d->desc.n_relax;
-    if (kind == FW2_DEVICE && (uintptr_t)buf % 4 == 0) {   // one launch moves every selected array
+    const uint64_t arrays = ((mask & FW2_FIELD_P) ? 1 : 0) + ((mask & FW2_FIELD_V) ? nd : 0) +
+                            ((mask & FW2_FIELD_PSI1) ? nd * L : 0) + ((mask & FW2_FIELD_PSI2) ? nd * L : 0);
+    if (kind == FW2_DEVICE && (uintptr_t)buf % 4 == 0 && device_range(buf, arrays * (uint64_t)d->npts() * 4)) {
+        // one launch moves every selected array
         const fw2::StepArgs &a = d->args;
         fw2::PlaneSet s;
         std::memset(&s, 0, sizeof(s));

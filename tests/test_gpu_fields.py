@@ -45,6 +45,22 @@ def test_device_fields_equal_host_fields(shape, offset):
         dom.destroy_domain()
 
 
+def test_device_fields_in_host_memory_go_by_copies():
+    """A buffer given as device memory that no kernel should address directly
+    (here pinned host memory) moves by copies, with the same values."""
+    import torch
+    dom, values = _domain((37, 11), 2)
+    n = dom.field_numel(fw2.FIELD_ALL)
+    buf = torch.as_tensor(values[:n]).pin_memory()
+    fw2._check(fw2.lib().fw2_write_fields(dom._h, fw2.FIELD_ALL, buf.data_ptr(), fw2.DEVICE))
+    by_device = dom.read_fields(fw2.FIELD_ALL)
+    dom.write_fields(dom.field_views(values[:n], fw2.FIELD_ALL), fw2.FIELD_ALL)
+    by_host = dom.read_fields(fw2.FIELD_ALL)
+    for k in by_host:
+        assert np.array_equal(by_device[k], by_host[k]), k
+    dom.destroy_domain()
+
+
 @pytest.mark.parametrize("n", [(64, 64, 64), (45, 30, 70), (130, 9, 40), (33, 8, 5), (96, 40, 3)])
 @pytest.mark.parametrize("L", [2, 5])
 def test_3d_tile_and_march_choice_does_not_change_results(n, L, monkeypatch):
