@@ -61,6 +61,41 @@ def test_device_fields_in_host_memory_go_by_copies():
     dom.destroy_domain()
 
 
+@pytest.mark.parametrize("shape,L", [((5, 9), 1), ((300, 41), 4), ((12, 6, 5), 2), ((70, 5, 3), 6)])
+@pytest.mark.parametrize("offset", [0, 60, 1])      # floats past 256 bytes: on 16 bytes, on 16 bytes, not
+def test_state_blocks_move_whole(shape, L, offset):
+    """save_state and load_state move the block's bytes, and nothing beside it,
+    whatever the buffer's alignment; captured, every replay does so again."""
+    import torch
+    prob = W.homogeneous(shape, L=L)
+    stream = torch.cuda.Stream(device="cuda:0")
+    with torch.cuda.stream(stream):
+        dom = fw2.from_problem(prob, device="cuda:0", stream=stream)
+        n = dom.state_bytes() // 4
+        rng = np.random.default_rng(n)
+        values = torch.as_tensor(rng.standard_normal(n).astype(np.float32)).to("cuda:0")
+        src = torch.zeros(n + offset, device="cuda:0")[offset:]
+        full = torch.full((n + 2 * 64,), -7.0, device="cuda:0")
+        dst = full[offset:offset + n]
+        src.copy_(values)
+        dom.load_state(src, 3)
+        dom.save_state(dst)
+        stream.synchronize()
+        assert torch.equal(dst, values) and bool((full[offset + n:] == -7.0).all())
+        assert bool((full[:offset] == -7.0).all()) and dom.current_step() == 3
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            dom.load_state(src, 0)
+            dom.save_state(dst)
+        for k in range(3):
+            src.copy_(values * (k + 2))
+            full.fill_(0.0)
+            graph.replay()
+            stream.synchronize()
+            assert torch.equal(dst, values * (k + 2)), k
+    dom.destroy_domain()
+
+
 @pytest.mark.parametrize("n", [(64, 64, 64), (45, 30, 70), (130, 9, 40), (33, 8, 5), (96, 40, 3)])
 @pytest.mark.parametrize("L", [2, 5])
 def test_3d_tile_and_march_choice_does_not_change_results(n, L, monkeypatch):
