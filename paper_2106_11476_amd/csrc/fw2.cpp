@@ -198,7 +198,11 @@ void make_layout(const fw2_domain_desc *d, Layout *ly)
 // 64^3 20.8 us against 220 (rows = 2), 256 x 256 x 64 135 against 246
 // (rows = 16), 160^3 138 against 250 (32 x 8, rows = 16), 203 x 149 x 177,
 // L = 3 264 against 327 (32 x 8, rows = 12), 300 x 200 x 100, L = 4 315
-// against 400 (rows = 8); 512^3 4.44 ms with 64, 128 or 256 planes.  The
+// against 400 (rows = 8); 512^3 4.44 ms with 64, 128 or 256 planes.  Where
+// 64 x 8 x 64 gives every CU the same number of blocks, two or more, to within
+// 3%, it stays: the cost above favours shorter marches that only add halo
+// planes (256^3 556 us against 573 with 32 planes, L = 4 870 against 897;
+// 320^3 1112 / 1119; but 384^3, 3.7% uneven, 1960 / 1911 with 24).  The
 // 32 x 8 tile wins where it pads x less; at equal padding it is 7% slower
 // (145 against 135 us at 256 x 256 x 64), hence its factor.  More than four
 // mechanisms have the 64 x 8 tile only.
@@ -206,6 +210,10 @@ fw2::KernelConfig sweep3d_config(const fw2::Geometry &g, int L)
 {
     constexpr int kCUs = 256;
     fw2::KernelConfig best{3, 64, 64};
+    const int64_t cols64 = (int64_t)((g.n[0] + 63) / 64) * ((g.n[1] + 7) / 8);
+    const int64_t turns = (cols64 * ((g.n[2] + 63) / 64) + kCUs - 1) / kCUs;
+    if (turns >= 2 && turns * kCUs * 64 * 100 <= cols64 * g.n[2] * 103 && (g.n[0] + 63) / 64 * 2 == (g.n[0] + 31) / 32)
+        return best;
     double best_cost = HUGE_VAL;
     for (int tile = 0; tile < (L <= 4 ? 2 : 1); ++tile) {
         const int bx = tile == 0 ? 64 : 32, waves = tile == 0 ? 8 : 4;
@@ -305,7 +313,8 @@ bool phase_adds_sources(const fw2_domain *d)
     const fw2::KernelConfig &kc = d->kc;
     if (kc.variant == 0) return false;
     if (g.ndim == 2) {
-        const int64_t tiles = (int64_t)((g.n[0] + 63) / 64) * ((g.n[1] + 7) / 8);
+        const int rows = kc.rows < 8 ? kc.rows : 8;
+        const int64_t tiles = (int64_t)((g.n[0] + 63) / 64) * ((g.n[1] + rows - 1) / rows);
         return d->src.n <= fw2::kTileSources && tiles * d->src.n <= kScanPairs;
     }
     // 3D: blocks of one column tile by kc.rows planes (16 x 8 the least tile)
@@ -851,13 +860,15 @@ fw2_status fw2_create_domain(const fw2_domain_desc *desc, void *dev_workspace, u
         a.w1[ax] = a.w2[ax] = nullptr;
     }
 
-    d->kc = nd == 2 ? fw2::KernelConfig{5, 64, 8} : sweep3d_config(g, L);
+    // 2D tiles of 8 rows; of 4 where more than four mechanisms stream from HBM
+    // (step_t2.hip has both sides; 1237 x 893, L = 8, in the cache, keeps 8)
+    d->kc = nd == 2 ? fw2::KernelConfig{5, 64, L > 4 && a.stream ? 4 : 8} : sweep3d_config(g, L);
     if (ly.shadow) d->one = fw2::KernelConfig{4, 64, one_launch_rows(g)};
     if (const char *ev = std::getenv("FW2_KERNEL_CONFIG")) {      // "variant,bx,rows[,by]" (tuning runs)
         int v = 0, bx = 0, ry = 0, by = 0;
         const int nparsed = std::sscanf(ev, "%d,%d,%d,%d", &v, &bx, &ry, &by);
         const bool parsed = nparsed == 3 || nparsed == 4;
-        const bool ok2 = nd == 2 && by == 0 && (v == 0 || (v == 5 && (ry == 8 || ry == 16))) && (bx == 64 || bx == 128 || bx == 256);
+        const bool ok2 = nd == 2 && by == 0 && (v == 0 || (v == 5 && (ry == 8 || ry == 16 || (ry == 4 && L > 4)))) && (bx == 64 || bx == 128 || bx == 256);
         if (parsed && v == 4 && by == 0 && ly.shadow && (ry == 8 || ry == 16)) d->one = fw2::KernelConfig{4, bx, ry};
         const bool tile3 = by == 0 ? (bx == 16 || bx == 32 || bx == 64)
                                    : (v == 3 && ((bx == 64 && by == 4) || (bx == 32 && by == 8)));

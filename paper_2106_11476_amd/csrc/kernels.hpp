@@ -104,8 +104,9 @@ struct StepArgs {
 // plane ahead, the point's own values at the top of their plane.
 // 2D: variant 4 (at most four mechanisms), a whole step out of place in one
 // launch of 64 x `rows` tiles (step_f2.hip), passed to launch_pressure;
-// variant 5, the phases from LDS tiles of 64 x `rows` (step_t2.hip), the
-// pressure phase adding the sources in a.src.
+// variant 5, the phases from LDS tiles of 64 x `rows` (step_t2.hip; 4 rows only
+// with more than four mechanisms), the pressure phase adding the sources in
+// a.src.
 struct KernelConfig {
     int variant;
     int bx;

@@ -110,3 +110,17 @@ def test_grids_around_the_cache_limits_equal_the_per_point_kernels(shape, L, mon
     got, _ = _run(prob, None, monkeypatch, 4, (3,), state)
     for k in ref:
         assert np.array_equal(ref[k], got[k]), k
+
+
+@pytest.mark.parametrize("shape,L,scheme,local,config", [
+    ((65, 17), 5, 1, 0, "5,64,4"), ((63, 5), 6, 0, 1, "5,64,4"), ((130, 3), 7, 0, 0, "5,64,4"),
+    ((64, 8), 8, 1, 1, "5,64,4"), ((2011, 1203), 8, 1, 0, None)])
+def test_four_row_tiles_equal_the_per_point_kernels(shape, L, scheme, local, config, monkeypatch):
+    """More than four mechanisms: tiles of four rows at their edges, and chosen
+    by a grid whose arrays (377 MB) pass the cache."""
+    prob = _problem(shape, L, scheme, local, 6)
+    state = W.random_state(2, L, shape, seed=3)
+    ref, _ = _run(prob, "0,64,8", monkeypatch, 4, (3,), state)
+    got, _ = _run(prob, config, monkeypatch, 4, (3,), state)
+    for k in ref:
+        assert np.array_equal(ref[k], got[k]), k
