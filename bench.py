@@ -34,9 +34,11 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0   # MI355X HBM3E, 8 TB/s
 XGMI_LINK_GBS = 153.0   # one xGMI link, one direction
 CSRC = os.path.join(ROOT, "paper_2106_11476_amd", "csrc")
-# the step kernels are templates in step_kernels.hpp over the layout of kernels.hpp
-KERNEL_SOURCE = [os.path.join(CSRC, "step_kernels.hpp"), os.path.join(CSRC, "kernels.hpp")]
-ADJOINT_SOURCE = os.path.join(CSRC, "adjoint.hip")
+# the step kernels: the 3D sweeps of step_kernels.hpp and the 2D tiles of
+# tile2d.hpp in step_t2.hip and step_f2.hip, over the layout of kernels.hpp
+KERNEL_SOURCE = [os.path.join(CSRC, f) for f in ("step_kernels.hpp", "kernels.hpp", "tile2d.hpp",
+                                                 "step_t2.hip", "step_f2.hip")]
+ADJOINT_SOURCE = [os.path.join(CSRC, f) for f in ("adjoint.hip", "tile2d.hpp")]
 ADJOINT_WORKLOAD = "inversion_2d_1536"
 PROFILES = os.path.join(ROOT, "profiles")
 
@@ -671,7 +673,7 @@ def summarize_adjoint(stats_db, fetch_db, write_db, copy_bytes, commands):
         fh.write("\n".join(lines) + "\n")
     # the steady reverse step: velocity kernel (deferred A3), receivers,
     # pressure kernel with the fused A0 of the step before, sources
-    parts = [("velocity", "adj_velocity<2, 2, true>"), ("pressure", "adj_pressure<2, 2, true>"),
+    parts = [("velocity", "adj_velocity_tile<2, "), ("pressure", "adj_pressure_tile<2, true, "),
              ("receivers", "adj_receivers("), ("sources", "adj_sources(")]
     txt = ["HBM traffic of one reverse step of the adjoint (2D, L = 2) on the 1536^2 inversion workload",
            "commands:"] + ["  " + c for c in commands]
