@@ -296,7 +296,11 @@ fw2_status fw2_adjoint_gradient(fw2_domain *dom, float *dst, int32_t dst_kind);
  *     step < n_steps[k]; a domain that leaves the set gets its step counter
  *     back (fw2_current_step stays exact).  n = 0 empties the batch.
  *   fw2_batch_step: n steps of every active domain, asynchronously on the
- *     batch stream (the domains' own streams are not used meanwhile).
+ *     batch stream (the domains' own streams are not used meanwhile).  Each
+ *     call goes on from the domains' own step counters: between calls, a
+ *     member may be reloaded (fw2_load_state), set to another step
+ *     (fw2_set_current_step) or stepped by itself, once the work on the batch
+ *     stream has finished; the batch stream must run after that work.
  *   fw2_batch_set_tile: wanted tile, cols = 64 or 256 columns by rows >= 1
  *     rows; only while the batch is empty.  The kernels' tiles are 64 columns
  *     by 8 rows, or by 16 where more than 1024 points are wanted.

@@ -192,6 +192,17 @@ __global__ void __launch_bounds__(256) batch_sources(const BatchTable *__restric
     }
 }
 
+// The entries' steps from the domains' own counters, once per call: the caller
+// may have loaded a state, set a counter, stepped a member alone or replayed a
+// graph of its own since.  One launch of one wavefront a call, so that the
+// tiles of every step need not follow 64 pointers to find their entry's step
+// (that chain is a second memory latency a tile).
+__global__ void __launch_bounds__(64) batch_take_steps(BatchTable *W)
+{
+    const int d = threadIdx.x;
+    if (d < W->n) W->next[d] = *W->e[d].rcv.step;
+}
+
 template <bool PRESSURE, int TY>
 void launch_batch_phase(BatchTable *T, int n_entries, unsigned blocks, hipStream_t st)
 {
@@ -218,7 +229,9 @@ void launch_batch_rows(BatchTable *T, int n_entries, bool sources, unsigned bloc
 hipError_t launch_batch_step(const BatchTable *T, int n_entries_max, int tile, unsigned blocks, hipStream_t st)
 {
     BatchTable *t = const_cast<BatchTable *>(T);
-    if ((tile & ~kBatchSources) == 8)
+    if (tile == kBatchTakeSteps)
+        hipLaunchKernelGGL(batch_take_steps, dim3(1), dim3(kMaxBatch), 0, st, t);
+    else if ((tile & ~kBatchSources) == 8)
         launch_batch_rows<8>(t, n_entries_max, (tile & kBatchSources) != 0, blocks, st);
     else
         launch_batch_rows<16>(t, n_entries_max, (tile & kBatchSources) != 0, blocks, st);

@@ -1527,7 +1527,6 @@ fw2_status fw2_batch_set_domains(fw2_batch *b, int32_t n, fw2_domain *const *dom
             T.nbx[m] = (d->ly.geo.n[0] + 63) / 64;
             T.key[m] = fw2::batch_key(d->desc.n_relax, d->desc.relax_scheme);
             T.n_steps[m] = n_steps[k];
-            T.next[m] = d->step;
             tiles += T.nbx[m] * ((d->ly.geo.n[1] + ty - 1) / ty);
             m++;
         }
@@ -1561,6 +1560,7 @@ fw2_status fw2_batch_step(fw2_batch *b, int32_t n)
     if (!b) return fail(FW2_E_STATE, "batch is NULL");
     if (n < 0) return fail(FW2_E_INVALID, "n < 0");
     if (n == 0 || b->doms.empty()) return FW2_OK;
+    FW2_HIP(fw2::launch_batch_step(b->dev, b->max_domains, fw2::kBatchTakeSteps, b->blocks, b->stream));
     int32_t left = n;
     if (b->graph_chunk > 0 && n >= b->graph_chunk) {
         if (!b->graph) {

@@ -140,8 +140,9 @@ struct BatchTable {
     int32_t class_begin[4], class_end[4];
     // What a block needs to find its tile's entry and whether it is active,
     // one lane per entry: the first tile, tiles per row, mechanisms and memory
-    // scheme (batch_key), the step to stop at, the next step (the device
-    // counter's value between steps) and the step under way.
+    // scheme (batch_key), the step to stop at, the next step (the domain's
+    // device counter, taken anew at the start of every call) and the step
+    // under way.
     int32_t tile_base[kMaxBatch], nbx[kMaxBatch], key[kMaxBatch];
     long long n_steps[kMaxBatch], next[kMaxBatch], now[kMaxBatch];
     BatchEntry e[kMaxBatch];
@@ -174,8 +175,9 @@ inline unsigned batch_code(int tiles, int c)
 
 // One step of every entry.  tile: the tile rows (8 or 16), with kBatchSources
 // where an entry has more sources than the tiles add; blocks: batch_code of
-// every class, or-ed.
-constexpr int kBatchSources = 256;
+// every class, or-ed.  tile = kBatchTakeSteps instead moves no entry and takes
+// their steps from the domains' counters.
+constexpr int kBatchSources = 256, kBatchTakeSteps = 512;
 hipError_t launch_batch_step(const BatchTable *dev_table, int n_entries_max, int tile, unsigned blocks,
                              hipStream_t stream);
 // The library's own batch table on `device` (the current device), for a
