@@ -280,6 +280,7 @@ struct fw2_domain {
     fw2::SparseArgs src, rcv;
     hipStream_t stream = nullptr;
     hipStream_t capture = nullptr;
+    int device = -1;                 // that of the workspace (-1: not known)
     int64_t step = 0;
     int graph_chunk = 32;
     hipGraphExec_t graph = nullptr;
@@ -469,17 +470,27 @@ fw2_status copy_box(fw2_domain *d, float *dev_base, void *packed, bool to_device
     return FW2_OK;
 }
 
-// Whether a kernel can reach all of [buf, buf + bytes): memory of the current
-// device inside one allocation.  Any other buffer is left to the copy calls,
-// which serve it or return an error.
-bool device_range(const void *buf, uint64_t bytes)
+// The device of a pointer into device memory; -1 for any other pointer.
+int device_of(const void *p)
 {
     hipPointerAttribute_t at;
-    int dev = -1;
+    if (hipPointerGetAttributes(&at, p) == hipSuccess && at.type == hipMemoryTypeDevice) return at.device;
+    (void)hipGetLastError();
+    return -1;
+}
+
+// Whether a kernel on the domain's stream can reach all of [buf, buf + bytes):
+// memory of the domain's own device inside one allocation (and, on the null
+// stream, that device current, since the launch goes to the current one).  Any
+// other buffer, another GPU's memory among them, is left to the copy calls,
+// which serve it or return an error.
+bool device_range(const fw2_domain *d, const void *buf, uint64_t bytes)
+{
+    int cur = -1;
     hipDeviceptr_t base = nullptr;
     size_t size = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipPointerGetAttributes(&at, buf) != hipSuccess ||
-        at.type != hipMemoryTypeDevice || at.device != dev ||
+    if (d->device < 0 || device_of(buf) != d->device) return false;
+    if ((!d->stream && (hipGetDevice(&cur) != hipSuccess || cur != d->device)) ||
         hipMemGetAddressRange(&base, &size, const_cast<void *>(buf)) != hipSuccess) {
         (void)hipGetLastError();
         return false;
@@ -502,7 +513,7 @@ int64_t state_floats(const fw2_domain *d)
 fw2_status copy_state(fw2_domain *d, void *block, bool out)
 {
     const size_t bytes = (size_t)state_floats(d) * 4;
-    if ((uintptr_t)block % 16 == 0 && device_range(block, bytes)) {
+    if ((uintptr_t)block % 16 == 0 && device_range(d, block, bytes)) {
         fw2::Geometry g = d->ly.geo;
         g.n[0] = 64;
         g.n[1] = (int32_t)(g.stride / 64);
@@ -534,7 +545,7 @@ fw2_status transfer_fields(fw2_domain *d, uint32_t mask, void *buf, int32_t kind
     const int nd = g.ndim, L = d->desc.n_relax;
     const uint64_t arrays = ((mask & FW2_FIELD_P) ? 1 : 0) + ((mask & FW2_FIELD_V) ? nd : 0) +
                             ((mask & FW2_FIELD_PSI1) ? nd * L : 0) + ((mask & FW2_FIELD_PSI2) ? nd * L : 0);
-    if (kind == FW2_DEVICE && (uintptr_t)buf % 4 == 0 && device_range(buf, arrays * (uint64_t)d->npts() * 4)) {
+    if (kind == FW2_DEVICE && (uintptr_t)buf % 4 == 0 && device_range(d, buf, arrays * (uint64_t)d->npts() * 4)) {
         // one launch moves every selected array
         const fw2::StepArgs &a = d->args;
         fw2::PlaneSet s;
@@ -677,6 +688,7 @@ fw2_status fw2_create_domain(const fw2_domain_desc *desc, void *dev_workspace, u
     d->ly = ly;
     d->ws = (uint8_t *)dev_workspace;
     d->stream = (hipStream_t)desc->stream;
+    d->device = device_of(dev_workspace);
     d->counter = (long long *)d->ws;
     d->flag = (int *)(d->ws + 8);
 
