@@ -133,12 +133,22 @@ typedef struct {
  * computation; validates desc).  Returns FW2_E_INVALID for a bad desc. */
 fw2_status fw2_workspace_bytes(const fw2_domain_desc *desc, uint64_t *bytes);
 
+/* The same with room for a second state block where the library can use one:
+ * small 2D grids (a step's arrays and the block within the last-level cache,
+ * at most four mechanisms) then step out of place in one launch instead of
+ * two, 1.1 to 1.3 times as fast, bitwise equal.  Up to 1.8 times the bytes of
+ * fw2_workspace_bytes; equal to them for every other domain.  Domains that are
+ * only stepped in a batch have no use for it. */
+fw2_status fw2_workspace_bytes_full(const fw2_domain_desc *desc, uint64_t *bytes);
+
 /* Create a domain (Sec. 3 setup: stencil weights from r, per-tissue and
  * per-boundary-position memory coefficients from Eqs. relaxation_a / _b and
  * Table 1's profiles, medium values from c, rho, beta).
- *   dev_workspace: caller-owned device buffer of at least fw2_workspace_bytes,
- *     256-byte aligned; it must outlive the domain.  The library performs no
- *     device allocation of its own beyond HIP events and graphs.
+ *   dev_workspace: caller-owned device buffer of workspace_bytes bytes, at
+ *     least fw2_workspace_bytes (from fw2_workspace_bytes_full on, the second
+ *     state block is used), 256-byte aligned; it must outlive the domain.  The
+ *     library performs no device allocation of its own beyond HIP events and
+ *     graphs.
  *   The host maps are read during the call and may be freed afterwards.
  *   All fields start at zero; the step counter starts at 0.
  *   Rejects a time step above the scheme's stability limit (FW2_E_INVALID). */

@@ -50,7 +50,8 @@ struct Layout {
     uint64_t tab_off[2][3];    // [nabla-1][axis] (b, c) tables
     uint64_t w_off[2][3];      // [nabla-1][axis] w tables
     int n_slots[2][3];
-    uint64_t total;
+    uint64_t total;            // bytes without the shadow
+    uint64_t full;             // bytes with it (grids of one_launch_size; else total)
 };
 
 bool finite_pos(double x) { return std::isfinite(x) && x > 0.0; }
@@ -125,8 +126,8 @@ fw2_status validate_scalars(const fw2_domain_desc *d)
 // hint: plain accesses gain 7% at 126^3 and lose from 140^3 on.
 constexpr int64_t kCacheBytes = (int64_t)240 << 20;
 
-// 2D grids advanced by one launch a step, out of place (step_f2.hip; their
-// workspace holds a second state block): those whose two state blocks and
+// 2D grids advanced by one launch a step, out of place (step_f2.hip; in a
+// workspace with room for a second state block): those whose two state blocks and
 // medium stay in the cache, and with more than two mechanisms only while every
 // 64 x 16 tile has a CU of its own.  Measured, us per step, two phases against
 // one launch: L = 2 128^2 6.4 / 5.0, 480^2 9.4 / 8.0, 1024^2 25.9 / 23.4,
@@ -160,9 +161,7 @@ void make_layout(const fw2_domain_desc *d, Layout *ly)
     g.origin = (d->ndim == 3 ? H * g.plane : 0) + H * g.pitch + H;
     const int L = d->n_relax;
     const int n_state = 1 + d->ndim + 2 * d->ndim * L;
-    const bool small = one_launch_size(d, g.stride);
-    ly->n_float = n_state + 3 + (small ? n_state : 0);     // state, medium, shadow of the state
-    ly->shadow = small ? (int64_t)(n_state + 3) * g.stride : 0;
+    ly->n_float = n_state + 3;                             // state, medium
     ly->float_base = kAlign + kAlign - (uint64_t)(H * 4) % kAlign;   // x = 0 on a 256-byte boundary
     uint64_t end = ly->float_base + (uint64_t)ly->n_float * g.stride * 4;
     end = align_up(end, kAlign);
@@ -186,7 +185,13 @@ void make_layout(const fw2_domain_desc *d, Layout *ly)
             ly->w_off[nab][a] = end;
             end = align_up(end + (uint64_t)ns * d->n_labels * 4, kAlign);
         }
-    ly->total = end;
+    ly->total = ly->full = end;
+    ly->shadow = 0;
+    if (one_launch_size(d, g.stride)) {
+        const uint64_t at = end + kAlign - (uint64_t)(H * 4) % kAlign;   // rows aligned as those of the state block
+        ly->shadow = (int64_t)(at - ly->float_base) / 4;
+        ly->full = align_up(at + (uint64_t)n_state * g.stride * 4, kAlign);
+    }
 }
 
 // Column tile and planes per block of the 3D sweeps.  A block marches over
@@ -404,10 +409,11 @@ fw2_status enqueue_step_on(fw2_domain *d, hipStream_t s)
 }
 
 // n steps.  One-launch steps go in pairs, to the shadow block and back, so
-// that the state always ends where the domain's fields are.
+// that the state always ends where the domain's fields are; without a shadow
+// block every step takes the phases.
 fw2_status enqueue_steps_on(fw2_domain *d, int32_t n, hipStream_t s)
 {
-    const int32_t m = one_launch(d) ? n & ~1 : 0;
+    const int32_t m = one_launch(d) && d->ly.shadow ? n & ~1 : 0;
     float *const st[2] = {d->args.p, d->args.p + d->ly.shadow};
     fw2_status r = FW2_OK;
     for (int32_t k = 0; k < m && r == FW2_OK; ++k) r = enqueue_one_launch(d, k, st[k & 1], st[1 - (k & 1)], s);
@@ -647,6 +653,17 @@ fw2_status fw2_workspace_bytes(const fw2_domain_desc *desc, uint64_t *bytes)
     return FW2_OK;
 }
 
+fw2_status fw2_workspace_bytes_full(const fw2_domain_desc *desc, uint64_t *bytes)
+{
+    fw2_status st = validate_scalars(desc);
+    if (st != FW2_OK) return st;
+    if (!bytes) return fail(FW2_E_INVALID, "bytes is NULL");
+    Layout ly;
+    make_layout(desc, &ly);
+    *bytes = ly.full;
+    return FW2_OK;
+}
+
 fw2_status fw2_create_domain(const fw2_domain_desc *desc, void *dev_workspace, uint64_t workspace_bytes,
                              fw2_domain **out)
 {
@@ -659,6 +676,7 @@ fw2_status fw2_create_domain(const fw2_domain_desc *desc, void *dev_workspace, u
     Layout ly;
     make_layout(desc, &ly);
     if (workspace_bytes < ly.total) return fail(FW2_E_NOMEM, "workspace too small");
+    if (workspace_bytes < ly.full) ly.shadow = 0;          // in place, two launches a step
 
     const fw2::Geometry &g = ly.geo;
     const int nd = desc->ndim, L = desc->n_relax;
@@ -702,7 +720,7 @@ fw2_status fw2_create_domain(const fw2_domain_desc *desc, void *dev_workspace, u
         if (e_ != hipSuccess) return cleanup(fail(FW2_E_HIP, std::string(#call) + ": " + hipGetErrorString(e_))); \
     } while (0)
 
-    FW2_HIP_C(hipMemsetAsync(d->ws, 0, ly.total, d->stream));
+    FW2_HIP_C(hipMemsetAsync(d->ws, 0, ly.shadow ? ly.full : ly.total, d->stream));
     FW2_HIP_C(hipStreamSynchronize(d->stream));     // the uploads below use blocking copies
 
     float *fb = (float *)(d->ws + ly.float_base);
@@ -875,13 +893,13 @@ fw2_status fw2_create_domain(const fw2_domain_desc *desc, void *dev_workspace, u
     // 2D tiles of 8 rows; of 4 where more than four mechanisms stream from HBM
     // (step_t2.hip has both sides; 1237 x 893, L = 8, in the cache, keeps 8)
     d->kc = nd == 2 ? fw2::KernelConfig{5, 64, L > 4 && a.stream ? 4 : 8} : sweep3d_config(g, L);
-    if (ly.shadow) d->one = fw2::KernelConfig{4, 64, one_launch_rows(g)};
+    if (one_launch_size(desc, g.stride)) d->one = fw2::KernelConfig{4, 64, one_launch_rows(g)};
     if (const char *ev = std::getenv("FW2_KERNEL_CONFIG")) {      // "variant,bx,rows[,by]" (tuning runs)
         int v = 0, bx = 0, ry = 0, by = 0;
         const int nparsed = std::sscanf(ev, "%d,%d,%d,%d", &v, &bx, &ry, &by);
         const bool parsed = nparsed == 3 || nparsed == 4;
         const bool ok2 = nd == 2 && by == 0 && (v == 0 || (v == 5 && (ry == 8 || ry == 16 || (ry == 4 && L > 4)))) && (bx == 64 || bx == 128 || bx == 256);
-        if (parsed && v == 4 && by == 0 && ly.shadow && (ry == 8 || ry == 16)) d->one = fw2::KernelConfig{4, bx, ry};
+        if (parsed && v == 4 && by == 0 && d->one.variant == 4 && (ry == 8 || ry == 16)) d->one = fw2::KernelConfig{4, bx, ry};
         const bool tile3 = by == 0 ? (bx == 16 || bx == 32 || bx == 64)
                                    : (v == 3 && ((bx == 64 && by == 4) || (bx == 32 && by == 8)));
         const bool ok3 = nd == 3 && (v == 0 || ((v >= 1 && v <= 3) && tile3));

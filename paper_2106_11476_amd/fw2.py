@@ -26,7 +26,7 @@ LOW, HIGH = 0, 1
 PHASE_PRESSURE, PHASE_VELOCITY = 0, 1
 MAX_LABELS = 256
 
-EXPORTS = ["fw2_workspace_bytes", "fw2_create_domain", "fw2_add_source", "fw2_add_receivers",
+EXPORTS = ["fw2_workspace_bytes", "fw2_workspace_bytes_full", "fw2_create_domain", "fw2_add_source", "fw2_add_receivers",
            "fw2_step", "fw2_read_fields", "fw2_write_fields", "fw2_current_step",
            "fw2_set_current_step", "fw2_set_stream", "fw2_set_graph_chunk", "fw2_enable_kernel_timing",
            "fw2_get_kernel_timing", "fw2_check_finite", "fw2_last_error", "fw2_destroy_domain",
@@ -73,6 +73,7 @@ def lib():
         vp, i32, i64, u32, u64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_uint32, ctypes.c_uint64
         sig = {
             "fw2_workspace_bytes": [ctypes.POINTER(DomainDesc), ctypes.POINTER(u64)],
+            "fw2_workspace_bytes_full": [ctypes.POINTER(DomainDesc), ctypes.POINTER(u64)],
             "fw2_create_domain": [ctypes.POINTER(DomainDesc), vp, u64, ctypes.POINTER(vp)],
             "fw2_add_source": [vp, i32, vp, vp, vp, i32, i32, vp],
             "fw2_add_receivers": [vp, i32, vp, vp, i64],
@@ -204,10 +205,13 @@ def label_relaxation_map(maps, n_relax):
     return label.reshape(m.shape[1:]), table[:int(n.value)].copy()
 
 
-def workspace_bytes(prob):
+def workspace_bytes(prob, second_block=False):
+    """Device bytes of a domain's workspace; second_block: with the second
+    state block that lets a small 2D grid step in one launch."""
     d, keep = make_desc(prob)
     out = ctypes.c_uint64(0)
-    _check(lib().fw2_workspace_bytes(ctypes.byref(d), ctypes.byref(out)))
+    size = lib().fw2_workspace_bytes_full if second_block else lib().fw2_workspace_bytes
+    _check(size(ctypes.byref(d), ctypes.byref(out)))
     return int(out.value)
 
 
@@ -216,9 +220,11 @@ class Domain:
 
     The workspace is a torch uint8 tensor; sources, receivers and traces are
     torch device tensors held by this object for as long as the library may
-    read them."""
+    read them.  second_block: the workspace has room for the second state
+    block that lets a small 2D grid step in one launch (up to 1.8 times the
+    memory; left out where the device has no room for it)."""
 
-    def __init__(self, prob, device="cuda", stream=None, device_maps=False):
+    def __init__(self, prob, device="cuda", stream=None, device_maps=False, second_block=True):
         import torch
         self.torch = torch
         self.device = torch.device(device)
@@ -246,11 +252,18 @@ class Domain:
                 d.label = dev["label"].data_ptr()
             d.map_kind = DEVICE
             keep.append(dev)
-        nbytes = ctypes.c_uint64(0)
+        nbytes, full = ctypes.c_uint64(0), ctypes.c_uint64(0)
         _check(lib().fw2_workspace_bytes(ctypes.byref(d), ctypes.byref(nbytes)))
-        self.workspace_bytes = int(nbytes.value)
+        _check(lib().fw2_workspace_bytes_full(ctypes.byref(d), ctypes.byref(full)))
+        self.workspace_bytes = int(full.value if second_block else nbytes.value)
         with torch.cuda.device(self.device):
-            self.workspace = torch.empty(self.workspace_bytes, dtype=torch.uint8, device=self.device)
+            try:
+                self.workspace = torch.empty(self.workspace_bytes, dtype=torch.uint8, device=self.device)
+            except torch.cuda.OutOfMemoryError:
+                if self.workspace_bytes == int(nbytes.value):
+                    raise
+                self.workspace_bytes = int(nbytes.value)
+                self.workspace = torch.empty(self.workspace_bytes, dtype=torch.uint8, device=self.device)
         # inputs prepared on the current stream are complete before the library
         # uses them on its own stream (other streams keep running)
         torch.cuda.current_stream(self.device).synchronize()

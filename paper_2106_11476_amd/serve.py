@@ -34,8 +34,8 @@ class Request:
 
 
 def footprint_bytes(prob, n_steps):
-    """Device bytes a request holds while resident: workspace, trace buffer,
-    source tables."""
+    """Device bytes a request holds while resident: workspace (without a second
+    state block), trace buffer, source tables."""
     ws = fw2.workspace_bytes(prob)
     n_rcv = max(len(prob.rcv_idx), 1)
     src = len(prob.src_idx) * (8 + 4 + 4) + np.asarray(prob.signals).size * 4
@@ -134,8 +134,15 @@ class Server:
         self.solo_points = int(solo_points)
         self.solo_chunk = int(solo_chunk) if solo_chunk else self.chunk
 
-    def _start(self, r):
-        dom = fw2.Domain(r.problem, device=self.device, stream=self.setup_stream)
+    def _start(self, r, held_bytes):
+        # the second state block is for domains stepped by themselves, where the
+        # budget has room for it beside everything held
+        second = r.problem.npts >= self.solo_points
+        if second:
+            extra = fw2.workspace_bytes(r.problem, second_block=True) - fw2.workspace_bytes(r.problem)
+            second = held_bytes + extra <= self.budget
+            r.footprint += extra if second else 0
+        dom = fw2.Domain(r.problem, device=self.device, stream=self.setup_stream, second_block=second)
         if len(r.problem.src_idx):
             dom.add_source(r.problem.src_idx, r.problem.src_sig, r.problem.src_w, r.problem.signals)
         dom.add_receivers(r.problem.rcv_idx, r.n_steps)
@@ -161,9 +168,10 @@ class Server:
         t0 = clock()
 
         def build_one():
+            held_bytes = sum(r.footprint for r, _ in active + solo + staged) + sum(r.footprint for r in pending)
             r = pending.pop(0)
             tb = clock()
-            staged.append((r, self._start(r)))
+            staged.append((r, self._start(r, held_bytes)))
             stats.t_build += clock() - tb
 
         while queue or active or solo or staged or pending:
@@ -303,7 +311,7 @@ def autotune_tile(problems, candidates=((256, 2), (256, 4), (256, 8), (64, 4), (
         raise ValueError("no candidate tile fits the problems")
     dev = torch.device(device)
     stream = torch.cuda.Stream(device=dev)
-    doms = [fw2.Domain(p, device=dev, stream=stream) for p in problems]
+    doms = [fw2.Domain(p, device=dev, stream=stream, second_block=False) for p in problems]
     best, timings = None, {}
     batch = fw2.Batch(max_domains=max(len(doms), 1), device=dev, stream=stream)
     for rows in candidates:

@@ -11,7 +11,7 @@ HOST = os.path.join(ROOT, "tests", "host")
 CSRC = os.path.join(ROOT, "paper_2106_11476_amd", "csrc")
 
 
-@pytest.mark.parametrize("driver", ["devices_driver.cpp"])
+@pytest.mark.parametrize("driver", ["devices_driver.cpp", "workspace_driver.cpp"])
 def test_host_routes(driver, tmp_path):
     from paper_2106_11476_amd import build
     exe = str(tmp_path / "driver")
@@ -21,3 +21,19 @@ def test_host_routes(driver, tmp_path):
     r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
     assert ": 0 failed" in r.stdout
+
+
+@pytest.mark.parametrize("shape,L", [((128, 128), 2), ((384, 260), 4), ((1024, 1024), 2), ((2400, 1500), 2), ((300, 200), 6)])
+def test_served_requests_hold_one_state_block(shape, L):
+    """The bytes a served request is admitted by: state and medium once (a
+    request stepped in a batch has no use for a second state block)."""
+    import numpy as np
+
+    import workloads as W
+    from paper_2106_11476_amd import fw2, serve
+    prob = W.homogeneous(shape, L=L)
+    prob.rcv_idx = np.zeros(0, np.int64)
+    stride = (shape[0] + 8 + 63) // 64 * 64 * (shape[1] + 8) * 4
+    arrays = 1 + 2 + 4 * L + 3
+    assert arrays * stride <= fw2.workspace_bytes(prob) < arrays * stride + (1 << 16)
+    assert serve.footprint_bytes(prob, 10) - fw2.workspace_bytes(prob) < 1 << 16
