@@ -647,7 +647,7 @@ hipError_t adjoint_step(const StepArgs &f, const SparseArgs &src, const SparseAr
         A.nblocks = A.nbx * A.nby;
         const dim3 tile(kTX * TY);
         const int rcv_blocks = (A.n_rcv + kTX * TY - 1) / (kTX * TY);
-        const bool in_tiles = sources && src.n <= kTileSources;
+        const bool in_tiles = sources && src.n <= kTileSources && (int64_t)A.nblocks * src.n <= kScanPairs;
         A.src = src;
         if (!in_tiles) A.src.n = 0;
         A.src_step = step - 1;

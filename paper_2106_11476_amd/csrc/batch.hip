@@ -98,7 +98,7 @@ __device__ __forceinline__ void batch_tile(const BatchEntry &e, int x0, int y0, 
 {
     const StepArgs &a = e.a;
     if constexpr (PRESSURE) {
-        const int n_src = step < a.src.n_t && a.src.n <= kTileSources ? a.src.n : 0;
+        const int n_src = step < a.src.n_t ? a.src.n : 0;
         pressure_tile<L, C, PP, TY>(a, x0, y0, a.src, n_src, step, lds.p);
     } else {
         velocity_tile<L, C, PP, TY>(a, x0, y0, lds.v);
@@ -145,7 +145,7 @@ __global__ void __launch_bounds__(kTX *TY, CLASS == 0 ? 8 : 4) batch_phase(const
             if (threadIdx.x == 0) W->now[d] = W->next[d];
             return;
         }
-        const SparseArgs &r = T->e[d].rcv;
+        const SparseArgs &r = T->e[d].a.rcv;
         const long long step = T->now[d];
         if (step < T->n_steps[d] && step < r.cap)
             for (int k = threadIdx.x; k < r.n; k += kTX * TY)
@@ -178,15 +178,17 @@ __global__ void __launch_bounds__(kTX *TY, CLASS == 0 ? 8 : 4) batch_phase(const
     }
 }
 
-// Sources of the entries that have more than the tiles take (one block each).
+// Sources that the tiles do not add: kSourceBlocks blocks an entry (one block
+// an entry was bound by its trips through a long list, 20 us for 4097 sources).
+constexpr int kSourceBlocks = 16;
 __global__ void __launch_bounds__(256) batch_sources(const BatchTable *__restrict__ T)
 {
-    const int d = blockIdx.x;
+    const int d = blockIdx.y;
     if (d >= T->n) return;
-    const SparseArgs &s = T->e[d].a.src;
+    const SparseArgs &s = T->e[d].src;
     const long long step = T->now[d];
-    if (s.n <= kTileSources || step >= T->n_steps[d] || step >= s.n_t) return;
-    for (int q = threadIdx.x; q < s.n; q += blockDim.x) {
+    if (step >= T->n_steps[d] || step >= s.n_t) return;
+    for (int q = blockIdx.x * 256 + threadIdx.x; q < s.n; q += kSourceBlocks * 256) {
         const int64_t pi = padded_index(s.geo, s.idx[q]);
         s.p[pi] = s.p[pi] + s.w[q] * s.signals[(int64_t)s.sig[q] * s.n_t + step];
     }
@@ -200,7 +202,7 @@ __global__ void __launch_bounds__(256) batch_sources(const BatchTable *__restric
 __global__ void __launch_bounds__(64) batch_take_steps(BatchTable *W)
 {
     const int d = threadIdx.x;
-    if (d < W->n) W->next[d] = *W->e[d].rcv.step;
+    if (d < W->n) W->next[d] = *W->e[d].a.rcv.step;
 }
 
 template <bool PRESSURE, int TY>
@@ -220,7 +222,7 @@ template <int TY>
 void launch_batch_rows(BatchTable *T, int n_entries, bool sources, unsigned blocks, hipStream_t st)
 {
     launch_batch_phase<true, TY>(T, n_entries, blocks, st);
-    if (sources) hipLaunchKernelGGL(batch_sources, dim3(n_entries), dim3(256), 0, st, T);
+    if (sources) hipLaunchKernelGGL(batch_sources, dim3(kSourceBlocks, n_entries), dim3(256), 0, st, T);
     launch_batch_phase<false, TY>(T, n_entries, blocks, st);
 }
 

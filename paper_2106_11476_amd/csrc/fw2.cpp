@@ -307,28 +307,26 @@ struct fw2_domain {
 
 namespace {
 
-// The velocity sweeps record the receivers in an extra block of their
-// launch; the one-thread-per-point kernel leaves them to a launch of their own.
-// Whether the pressure phase's tiles add the sources.  Every tile reads the
-// list: 21 M (tile, source) pairs cost 12 us a step (1280 sources at 4096 x
-// 2048), the launch that adds them otherwise 4.5 us, so up to 4 M pairs.
-constexpr int64_t kScanPairs = (int64_t)4 << 20;
+// Tiles of 64 columns by `rows` of a 2D grid.
+int64_t tiles_2d(const fw2::Geometry &g, int rows) { return (int64_t)((g.n[0] + 63) / 64) * ((g.n[1] + rows - 1) / rows); }
+
+// Whether the pressure phase's tiles add the sources.
 bool phase_adds_sources(const fw2_domain *d)
 {
     const fw2::Geometry &g = d->ly.geo;
     const fw2::KernelConfig &kc = d->kc;
     if (kc.variant == 0) return false;
-    if (g.ndim == 2) {
-        const int rows = kc.rows < 8 ? kc.rows : 8;
-        const int64_t tiles = (int64_t)((g.n[0] + 63) / 64) * ((g.n[1] + rows - 1) / rows);
-        return d->src.n <= fw2::kTileSources && tiles * d->src.n <= kScanPairs;
-    }
+    if (g.ndim == 2)
+        return d->src.n <= fw2::kTileSources && tiles_2d(g, kc.rows < 8 ? kc.rows : 8) * d->src.n <= fw2::kScanPairs;
     // 3D: blocks of one column tile by kc.rows planes (16 x 8 the least tile)
     const int by = kc.by ? kc.by : (kc.bx == 64 ? 8 : 16), bx = d->desc.n_relax > 4 ? 64 : kc.bx;
     const int64_t tiles = (int64_t)((g.n[0] + bx - 1) / bx) * ((g.n[1] + by - 1) / by) * ((g.n[2] + kc.rows - 1) / kc.rows);
-    return d->src.n <= fw2::kTileSources3 && tiles * d->src.n <= kScanPairs;
+    return d->src.n <= fw2::kTileSources3 && tiles * d->src.n <= fw2::kScanPairs;
 }
 
+// What the phases' launches take of the sources and receivers.  The velocity
+// tiles and sweeps record the receivers in an extra block of their launch; the
+// one-thread-per-point kernel leaves them to a launch of their own.
 void sync_sparse_args(fw2_domain *d)
 {
     d->args.src = d->src;
@@ -364,8 +362,13 @@ fw2_status enqueue_step(fw2_domain *d, TimingSlot *ts)
 }
 
 // Whether steps run as one launch each: decided by the grid when the domain
-// is created and by the number of sources; kernel timing takes the phases.
-bool one_launch(const fw2_domain *d) { return d->one.variant == 4 && !d->timing && d->src.n <= fw2::kTileSources; }
+// is created and by the number of sources (its tiles add them); kernel timing
+// takes the phases.
+bool one_launch(const fw2_domain *d)
+{
+    return d->one.variant == 4 && !d->timing && d->src.n <= fw2::kTileSources &&
+           tiles_2d(d->ly.geo, d->one.rows) * d->src.n <= fw2::kScanPairs;
+}
 
 // Step k of a run of one-launch steps from the state block at src to that at
 // dst: its sources are those k past the device counter, and it records the
@@ -1415,7 +1418,7 @@ struct fw2_batch {
     int rows = 4;
     int bx = 256;
     unsigned blocks = 0;                // blocks of each class launch (fw2::batch_code)
-    bool sources = false;               // an entry has more sources than the tiles add
+    bool sources = false;               // the sources are added by a launch of their own
     int static_device = -1;             // >= 0: the table is the library's own on this device
 };
 
@@ -1530,16 +1533,18 @@ fw2_status fw2_batch_set_domains(fw2_batch *b, int32_t n, fw2_domain *const *dom
     T.rows = b->rows;
     int tiles = 0, m = 0;
     bool sources = false;
-    int64_t bytes = 0;
+    int64_t bytes = 0, pairs = 0;
     for (int32_t k = 0; k < n; ++k) {
         fw2_domain *d = domains[k];
         bytes += (state_floats(d) + 3 * d->ly.geo.stride) * 4;
         sources |= d->src.n > fw2::kTileSources;
+        pairs += tiles_2d(d->ly.geo, tile_rows(b)) * d->src.n;
         // the domain's own queued work must be finished before the batch stream touches it
         FW2_HIP(hipStreamSynchronize(d->stream));
         b->doms.push_back(d);
         b->target.push_back(n_steps[k]);
     }
+    sources |= pairs > fw2::kScanPairs;
     const int32_t stream = bytes > kCacheBytes;     // the entries share the cache
     // entries grouped by launch class, so that each class launch walks only
     // its own tiles, spread over every XCD
@@ -1550,8 +1555,9 @@ fw2_status fw2_batch_set_domains(fw2_batch *b, int32_t n, fw2_domain *const *dom
             if (fw2::batch_class(d->desc.n_relax, d->args.local_stencil) != c) continue;
             T.e[m].a = d->args;
             T.e[m].a.stream = stream;
-            T.e[m].a.src = d->src;
-            T.e[m].rcv = d->rcv;
+            T.e[m].a.rcv = d->rcv;
+            T.e[m].a.src = T.e[m].src = d->src;
+            if (sources) T.e[m].a.src.n = 0;
             const int ty = tile_rows(b);
             T.tile_base[m] = tiles;
             T.nbx[m] = (d->ly.geo.n[0] + 63) / 64;

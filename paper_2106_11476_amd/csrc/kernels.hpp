@@ -120,15 +120,27 @@ struct KernelConfig {
 // domains are active.  A domain whose step counter has reached n_steps is
 // skipped (its counter keeps counting while it stays in the table).
 constexpr int kMaxBatch = 64;
-// The most sources the tiles of a 2D kernel add themselves (each reads the
-// list); more are added by a launch of their own.
+// Sources: added by the tiles of a kernel, each of which reads the list, or by
+// a launch of their own.  The tiles take them up to kTileSources (2D) or
+// kTileSources3 (3D sweeps, which list a tile's sources in LDS) and up to
+// kScanPairs pairs of a tile and a source (over all entries of a batch), where
+// the reading costs what the launch does.  us a step by the tiles / a launch
+// (the one-launch step / two phases): reverse step 1536^2, L = 2, 2.4 M pairs
+// 103.6 / 105.0, 4.7 M 104.2, 9.4 M 108.0, 19 M 112.0; one-launch step 1500^2,
+// L = 2, 2.3 M 47.8 / 52.3, 4.6 M 50.0 / 52.4, 9.2 M 54.1 / 52.5; 1900^2, L = 1,
+// 3.7 M 58.0 / 60.0, 7.3 M 61.0 / 59.8, 15 M 66.4 / 60.2; batch of one 2048^2,
+// L = 4, 4.2 M 137.7 / 138.9, 17 M 145.6 / 140.0, of eight 384^2, L = 3, 4.7 M
+// 45.0 / 43.4; two phases 4096 x 2048, L = 4, 21 M pairs 12 us a step more than
+// without sources, the launch 4.5.
 constexpr int32_t kTileSources = 4096;
-// The same for the 3D sweeps, which list a tile's sources in LDS.
 constexpr int32_t kTileSources3 = 1024;
+constexpr int64_t kScanPairs = (int64_t)4 << 20;
 
+// a.src holds the sources that the tiles add (n = 0: none), src those that a
+// launch of their own adds; a.rcv the receivers.
 struct BatchEntry {
     StepArgs a;
-    SparseArgs rcv;          // (the sources are a.src)
+    SparseArgs src;
 };
 
 struct BatchTable {
@@ -174,7 +186,7 @@ inline unsigned batch_code(int tiles, int c)
 }
 
 // One step of every entry.  tile: the tile rows (8 or 16), with kBatchSources
-// where an entry has more sources than the tiles add; blocks: batch_code of
+// where the sources are added by a launch of their own; blocks: batch_code of
 // every class, or-ed.  tile = kBatchTakeSteps instead moves no entry and takes
 // their steps from the domains' counters.
 constexpr int kBatchSources = 256, kBatchTakeSteps = 512;

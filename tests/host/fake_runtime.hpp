@@ -25,6 +25,7 @@ inline int copies = 0, packs = 0, unpacks = 0;       // row or block copies; pla
 inline int pressure_variant = -1;                    // of the last pressure launch
 inline int pressure_launches = 0, source_launches = 0;
 inline fw2::StepArgs pressure_args;
+inline int batch_tile = -1;                          // of the last batched step
 
 inline void *alloc(uint64_t bytes, int device)
 {
@@ -138,7 +139,11 @@ hipError_t launch_unpack(const PlaneSet &, const Geometry &, const float *, hipS
 }
 hipError_t launch_medium(const MediumArgs &, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_stream_probe(int, void *, uint64_t, hipStream_t) { return hipErrorNoDevice; }
-hipError_t launch_batch_step(const BatchTable *, int, int, unsigned, hipStream_t) { return hipSuccess; }
+hipError_t launch_batch_step(const BatchTable *, int, int tile, unsigned, hipStream_t)
+{
+    if (tile != kBatchTakeSteps) fake::batch_tile = tile;
+    return hipSuccess;
+}
 hipError_t claim_static_batch_table(int, BatchTable **, bool *) { return hipErrorNoDevice; }
 void release_static_batch_table(int) {}
 hipError_t launch_adjoint_step(const StepArgs &, const SparseArgs &, const SparseArgs &, int, const float *,
