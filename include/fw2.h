@@ -312,11 +312,13 @@ fw2_status fw2_adjoint_gradient(fw2_domain *dom, float *dst, int32_t dst_kind);
  *     (fw2_set_current_step) or stepped by itself, once the work on the batch
  *     stream has finished; the batch stream must run after that work.
  *   fw2_batch_set_tile: wanted tile, cols = 64 or 256 columns by rows >= 1
- *     rows; only while the batch is empty.  The kernels' tiles are 64 columns
- *     by 8 rows, or by 16 where more than 1024 points are wanted.
+ *     rows; only while the batch is empty.  The kernels have two: 64 columns by
+ *     8 rows, and 64 by 16, which 64 x 16 and more rows or 256 x 5 and more
+ *     ask for.
  * Errors: FW2_E_INVALID for bad arguments, FW2_E_UNSUPPORTED for 3D domains
- * and for domains with more than four mechanisms when the tile has 64
- * columns, FW2_E_HIP for runtime failures. */
+ * and for domains with more than four mechanisms when 64 columns were asked
+ * for (part of the interface, not of the kernels, which have the same tiles
+ * either way), FW2_E_HIP for runtime failures. */
 typedef struct fw2_batch fw2_batch;
 fw2_status fw2_batch_workspace_bytes(int32_t max_domains, uint64_t *bytes);
 fw2_status fw2_batch_create(int32_t max_domains, void *dev_workspace, uint64_t workspace_bytes,

@@ -1424,9 +1424,9 @@ struct fw2_batch {
 
 namespace {
 
-// Tile rows: the batched kernels have tiles of 64 columns by 8 or 16 rows, a
-// requested tile of more than 1024 points takes 16.
-int tile_rows(const fw2_batch *b) { return b->bx * b->rows > 1024 ? 16 : 8; }
+// Tile rows: the batched kernels have tiles of 64 columns by 8 or 16 rows.  16
+// are asked for as such (64 columns), or by more than 256 x 4.
+int tile_rows(const fw2_batch *b) { return b->rows >= (b->bx == 64 ? 16 : 5) ? 16 : 8; }
 
 int batch_tile(const fw2_batch *b) { return tile_rows(b) | (b->sources ? fw2::kBatchSources : 0); }
 
@@ -1500,7 +1500,6 @@ fw2_status fw2_batch_create(int32_t max_domains, void *dev_workspace, uint64_t w
     b->dev = (fw2::BatchTable *)dev_workspace;
     b->stream = (hipStream_t)stream;
     std::memset(&b->host, 0, sizeof(b->host));
-    b->host.rows = b->rows;
     hipError_t e = hipMemcpy(b->dev, &b->host, sizeof(b->host), hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         delete b;
@@ -1530,7 +1529,6 @@ fw2_status fw2_batch_set_domains(fw2_batch *b, int32_t n, fw2_domain *const *dom
     if (st != FW2_OK) return st;
     fw2::BatchTable &T = b->host;
     std::memset(&T, 0, sizeof(T));
-    T.rows = b->rows;
     int tiles = 0, m = 0;
     bool sources = false;
     int64_t bytes = 0, pairs = 0;
@@ -1570,7 +1568,6 @@ fw2_status fw2_batch_set_domains(fw2_batch *b, int32_t n, fw2_domain *const *dom
     }
     if (m != n) return fail(FW2_E_INVALID, "a domain of no launch class");
     T.n = n;
-    T.total_tiles = tiles;
     // the captured grids stay while every class has tiles as before and fills
     // at least half of its blocks (a block without a tile ends at once)
     bool fits = b->sources == sources;
@@ -1622,8 +1619,6 @@ fw2_status fw2_batch_set_tile(fw2_batch *b, int32_t cols, int32_t rows)
     b->bx = cols;
     b->rows = rows;
     if (tile_rows(b) != before) batch_drop_graph(b);
-    b->host.rows = rows;
-    FW2_HIP(hipMemcpy(b->dev, &b->host, sizeof(b->host), hipMemcpyHostToDevice));
     return FW2_OK;
 }
 
@@ -1649,7 +1644,6 @@ fw2_status fw2_batch_create_noalloc(int32_t max_domains, void *stream, fw2_batch
     b->static_device = device;
     b->stream = (hipStream_t)stream;
     std::memset(&b->host, 0, sizeof(b->host));
-    b->host.rows = b->rows;
     // the table keeps the last batch's contents: start from the empty table
     hipError_t e = hipMemcpy(b->dev, &b->host, sizeof(b->host), hipMemcpyHostToDevice);
     if (e != hipSuccess) {

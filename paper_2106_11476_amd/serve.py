@@ -297,13 +297,13 @@ def run_plain(requests, device="cuda:0", clock=time.perf_counter, on_done=None):
     return stats
 
 
-def autotune_tile(problems, candidates=((256, 2), (256, 4), (256, 8), (64, 4), (64, 8), (64, 16)),
-                  steps=32, device="cuda:0"):
-    """Pick the batched sweep's tile (columns, rows) by timing each candidate
+def autotune_tile(problems, candidates=((256, 4), (256, 8)), steps=32, device="cuda:0"):
+    """Pick the batched step's tile (columns, rows) by timing each candidate
     on a batch of zero-state copies of the given problems (sources are not
-    attached, so the fields stay zero and nothing is consumed).  Domains with
-    more than four mechanisms run in 256-column tiles only, so with such a
-    problem in the mix the 64-column candidates are left out."""
+    attached, so the fields stay zero and nothing is consumed).  The default
+    candidates ask for the two tiles that the kernels have (64 x 8 and 64 x 16).
+    Domains with more than four mechanisms are refused with 64 columns asked
+    for, so with such a problem in the mix those candidates are left out."""
     import torch
     if any(int(p.n_relax) > 4 for p in problems):
         candidates = tuple(c for c in candidates if c[0] == 256)

@@ -11,7 +11,7 @@ HOST = os.path.join(ROOT, "tests", "host")
 CSRC = os.path.join(ROOT, "paper_2106_11476_amd", "csrc")
 
 
-@pytest.mark.parametrize("driver", ["devices_driver.cpp", "workspace_driver.cpp", "sources_driver.cpp"])
+@pytest.mark.parametrize("driver", ["devices_driver.cpp", "workspace_driver.cpp", "sources_driver.cpp", "tiles_driver.cpp"])
 def test_host_routes(driver, tmp_path):
     from paper_2106_11476_amd import build
     exe = str(tmp_path / "driver")
@@ -37,3 +37,14 @@ def test_served_requests_hold_one_state_block(shape, L):
     arrays = 1 + 2 + 4 * L + 3
     assert arrays * stride <= fw2.workspace_bytes(prob) < arrays * stride + (1 << 16)
     assert serve.footprint_bytes(prob, 10) - fw2.workspace_bytes(prob) < 1 << 16
+
+
+def test_the_autotuner_times_each_kernel_once():
+    """Its default candidates ask for the two tiles that the batched kernels
+    have: 64 x 8, and 64 x 16 for more than 256 x 4."""
+    import inspect
+
+    from paper_2106_11476_amd import serve
+    tiles = inspect.signature(serve.autotune_tile).parameters["candidates"].default
+    rows = [16 if r >= (16 if c == 64 else 5) else 8 for c, r in tiles]
+    assert sorted(rows) == [8, 16]
