@@ -11,7 +11,8 @@ HOST = os.path.join(ROOT, "tests", "host")
 CSRC = os.path.join(ROOT, "paper_2106_11476_amd", "csrc")
 
 
-@pytest.mark.parametrize("driver", ["devices_driver.cpp", "workspace_driver.cpp", "sources_driver.cpp", "tiles_driver.cpp"])
+@pytest.mark.parametrize("driver", ["devices_driver.cpp", "workspace_driver.cpp", "sources_driver.cpp", "tiles_driver.cpp",
+                                    "limits_driver.cpp"])
 def test_host_routes(driver, tmp_path):
     from paper_2106_11476_amd import build
     exe = str(tmp_path / "driver")
