@@ -307,8 +307,12 @@ struct fw2_domain {
 
 namespace {
 
-// Tiles of 64 columns by `rows` of a 2D grid.
-int64_t tiles_2d(const fw2::Geometry &g, int rows) { return (int64_t)((g.n[0] + 63) / 64) * ((g.n[1] + rows - 1) / rows); }
+// Tiles of a 2D grid: 64 columns by 8 or 16 rows, 128 by 4.
+int64_t tiles_2d(const fw2::Geometry &g, int rows)
+{
+    const int cols = rows == 4 ? 128 : 64;
+    return (int64_t)((g.n[0] + cols - 1) / cols) * ((g.n[1] + rows - 1) / rows);
+}
 
 // Whether the pressure phase's tiles add the sources.
 bool phase_adds_sources(const fw2_domain *d)
@@ -893,8 +897,8 @@ fw2_status fw2_create_domain(const fw2_domain_desc *desc, void *dev_workspace, u
         a.w1[ax] = a.w2[ax] = nullptr;
     }
 
-    // 2D tiles of 8 rows; of 4 where more than four mechanisms stream from HBM
-    // (step_t2.hip has both sides; 1237 x 893, L = 8, in the cache, keeps 8)
+    // 2D tiles of 64 x 8; of 128 x 4 where more than four mechanisms stream from
+    // HBM (step_t2.hip has both sides; 1237 x 893, L = 8, in the cache, keeps 8)
     d->kc = nd == 2 ? fw2::KernelConfig{5, 64, L > 4 && a.stream ? 4 : 8} : sweep3d_config(g, L);
     if (one_launch_size(desc, g.stride)) d->one = fw2::KernelConfig{4, 64, one_launch_rows(g)};
     if (const char *ev = std::getenv("FW2_KERNEL_CONFIG")) {      // "variant,bx,rows[,by]" (tuning runs)

@@ -104,15 +104,24 @@ struct StepArgs {
 // plane ahead, the point's own values at the top of their plane.
 // 2D: variant 4 (at most four mechanisms), a whole step out of place in one
 // launch of 64 x `rows` tiles (step_f2.hip), passed to launch_pressure;
-// variant 5, the phases from LDS tiles of 64 x `rows` (step_t2.hip; 4 rows only
-// with more than four mechanisms), the pressure phase adding the sources in
-// a.src.
+// variant 5, the phases from LDS tiles of 64 x 8, 64 x 16 or (rows = 4, only
+// with more than four mechanisms) 128 x 4 (step_t2.hip), the pressure phase
+// adding the sources in a.src.
 struct KernelConfig {
     int variant;
     int bx;
     int rows;
     int by = 0;              // 3D: tile rows in y (0: the default of bx)
 };
+
+// Tile of block `bid` where XCD x (blocks dealt round-robin) takes one
+// contiguous band of the nblocks tiles and starts x * shift tiles into it, going
+// on at the band's start past its end.  A bijection of [0, nblocks).
+__host__ __device__ inline int shifted_tile(int bid, int nblocks, int shift)
+{
+    const int x = bid % 8, rem = nblocks % 8, count = nblocks / 8 + (x < rem ? 1 : 0);
+    return x * (nblocks / 8) + (x < rem ? x : rem) + (bid / 8 + x * shift) % count;
+}
 
 // Many 2D domains advanced by one launch per phase (batched serving).  The
 // table lives in device memory; the blocks of a grid sized for the tiles of

@@ -6,50 +6,83 @@ namespace fw2 {
 
 namespace {
 
-template <int L, bool C, bool PP, int TY>
-__global__ void __launch_bounds__(kTX *TY) pressure_tiles(const StepArgs a, int nbx, int nblocks)
+// The tile of a block: the eight XCDs take a contiguous band each, and (4 rows,
+// band_shift) XCD x starts x * shift tiles into it.
+template <int TY>
+__device__ __forceinline__ int tile_of_band(int bid, int nblocks, int shift)
 {
-    __shared__ PressureLds<TY> lds;
-    const int tile = tile_of_block(blockIdx.x, nblocks);
+    return TY == 4 && shift ? shifted_tile(bid, nblocks, shift) : tile_of_block(bid, nblocks);
+}
+
+template <int L, bool C, bool PP, int TY, int TX>
+__global__ void __launch_bounds__(TX *TY) pressure_tiles(const StepArgs a, int nbx, int nblocks, int shift)
+{
+    __shared__ PressureLds<TY, TX> lds;
+    const int tile = tile_of_band<TY>(blockIdx.x, nblocks, shift);
     long long step = 0;
     int n_src = 0;
     if (a.src.n > 0) {
         step = *a.src.step;
         n_src = step < a.src.n_t ? a.src.n : 0;
     }
-    pressure_tile<L, C, PP, TY>(a, (tile % nbx) * kTX, (tile / nbx) * TY, a.src, n_src, step, lds);
+    pressure_tile<L, C, PP, TY, TX>(a, (tile % nbx) * TX, (tile / nbx) * TY, a.src, n_src, step, lds);
 }
 
-template <int L, bool C, bool PP, int TY>
-__global__ void __launch_bounds__(kTX *TY) velocity_tiles(const StepArgs a, int nbx, int nblocks)
+template <int L, bool C, bool PP, int TY, int TX>
+__global__ void __launch_bounds__(TX *TY) velocity_tiles(const StepArgs a, int nbx, int nblocks, int shift)
 {
-    const int shift = a.rcv.step ? 1 : 0;            // with receivers, block 0 records them
-    if ((int)blockIdx.x < shift) {
+    const int rcv = a.rcv.step ? 1 : 0;              // with receivers, block 0 records them
+    if ((int)blockIdx.x < rcv) {
         record_receivers(a.rcv);
         return;
     }
-    __shared__ VelocityLds<TY> lds;
-    const int tile = tile_of_block((int)blockIdx.x - shift, nblocks);
-    velocity_tile<L, C, PP, TY>(a, (tile % nbx) * kTX, (tile / nbx) * TY, lds);
+    __shared__ VelocityLds<TY, TX> lds;
+    const int tile = tile_of_band<TY>((int)blockIdx.x - rcv, nblocks, shift);
+    velocity_tile<L, C, PP, TY, TX>(a, (tile % nbx) * TX, (tile / nbx) * TY, lds);
 }
 
-// LDS set aside for each block of the 4-row tiles, so that a CU holds five of
-// them.  Streaming 2 L + 5 arrays is bound by HBM, which serves fewer tiles in
-// flight better: us per step, 8 rows / 4 rows, eight blocks a CU / 4 rows, five
-// blocks: 4096 x 2048, L = 8 452 / 438 / 434; 6000 x 3000, L = 6 853 / 858 /
-// 845; 2048^2, L = 6 185 / 190 / 183; 3000 x 1500, L = 5 166 / 164 / 164.
-constexpr unsigned kReserve4 = 24000;
+// The tiles of more than four mechanisms whose arrays pass the cache: 128
+// columns by 4 rows, with LDS set aside so that a CU holds three blocks.
+// Streaming 2 L + 5 arrays is bound by HBM, which serves fewer tiles in flight
+// and longer rows better.  us per step, row sweeps of 256 columns by 4 rows /
+// 64 x 8 / 64 x 4 with five blocks a CU / 128 x 4 with three, L = 6 and 8:
+// 2000^2 170 / 174 / 168 / 165 and 212 / 225 / 216 / 210; 1000 x 4224 185 / - /
+// 189 / 179 and 232 / - / 240 / 228; 4096 x 2048 338 / 344 / 335 / 333 and 438 /
+// 452 / 432 / 427; 6000 x 3000 841 / 853 / 838 / 834 and 1073 / - / 1081 / 1060;
+// over 37 sizes of 1.6 to 18 M points 3.6% faster than the sweeps (64 x 4: 2.3%),
+// at most 1.2% slower where the rule below does not apply.
+constexpr int kTX4 = 128;
+constexpr unsigned kReserve4 = 40000;
+
+// Where the bands of neighbouring XCDs start just under or at 33 x 64 KiB apart
+// in each array, the eight streams meet in the same HBM channels; there each
+// XCD starts its band three tile rows further in than the one before (two to
+// eight rows do as well).  us per step, sweeps / 128 x 4 / shifted, L = 6 and 8:
+// 2048^2 (33.0) 179 / 181 / 174 and 231 / 239 / 223; 2100 x 2048 (33.0) 188 / 192 /
+// 180 and 243 / 246 / 230; 1900 x 2252 (32.8) 192 / 190 / 178 and 244 / 248 / 226;
+// 1400 x 3072 (33.0) 192 / 186 / 178 and 246 / 240 / 227; 1000 x 4224 (33.0) 185 /
+// 179 / 180 and 232 / 228 / 228.  On either side the shift loses: 2000 x 2048
+// (32.0) 172 / 165 / 181, 3000 x 1440 (33.05) 185 / 179 / 185, 1900 x 2284 (33.3)
+// 187 / 177 / 181, 2048 x 2112 (34.0) 184 / 174 / 178.
+int band_shift(const Geometry &g, int nbx, int nblocks)
+{
+    const int64_t apart = (int64_t)(nblocks / 8) * 4 * g.pitch * 4 / nbx;
+    return apart * 100 >= (int64_t)3275 * 65536 && apart * 100 <= (int64_t)3303 * 65536 ? 3 * nbx : 0;
+}
 
 template <int L, bool C, bool PP, int TY>
 hipError_t launch(const StepArgs &a, bool pressure, hipStream_t st)
 {
-    const int nbx = (a.geo.n[0] + kTX - 1) / kTX, nblocks = nbx * ((a.geo.n[1] + TY - 1) / TY);
+    constexpr int TX = TY == 4 ? kTX4 : kTX;
     constexpr unsigned reserve = TY == 4 ? kReserve4 : 0;
+    const int nbx = (a.geo.n[0] + TX - 1) / TX, nblocks = nbx * ((a.geo.n[1] + TY - 1) / TY);
+    const int shift = TY == 4 ? band_shift(a.geo, nbx, nblocks) : 0;
     if (pressure)
-        hipLaunchKernelGGL((pressure_tiles<L, C, PP, TY>), dim3(nblocks), dim3(kTX * TY), reserve, st, a, nbx, nblocks);
+        hipLaunchKernelGGL((pressure_tiles<L, C, PP, TY, TX>), dim3(nblocks), dim3(TX * TY), reserve, st, a, nbx, nblocks,
+                           shift);
     else
-        hipLaunchKernelGGL((velocity_tiles<L, C, PP, TY>), dim3(nblocks + (a.rcv.step ? 1 : 0)), dim3(kTX * TY), reserve,
-                           st, a, nbx, nblocks);
+        hipLaunchKernelGGL((velocity_tiles<L, C, PP, TY, TX>), dim3(nblocks + (a.rcv.step ? 1 : 0)), dim3(TX * TY), reserve,
+                           st, a, nbx, nblocks, shift);
     return hipGetLastError();
 }
 

@@ -1,4 +1,5 @@
-// 2D phases from LDS tiles of 64 columns x TY rows, one thread a point.
+// 2D phases from LDS tiles of TX = 64 (or 128) columns x TY rows, one thread a
+// point.
 //
 // A block issues every load of its tile at once (the stencil field's window
 // with its halo, the point's own values), so a tile costs one exposed load
@@ -11,6 +12,7 @@
 // 4096 x 2048, L = 4 247 / 235-243 (6.3 TB/s of its 182 B a point); 8192 x
 // 4096, L = 2 886 / 749.  Tiles of 16 rows: 254 at 4096 x 2048, L = 4, 762 at
 // 8192 x 4096, 287 against 290-300 at 3072^2, L = 3; of 4 rows 241, 787, 291.
+// (step_t2.hip has the tile of more than four mechanisms past the cache.)
 #pragma once
 
 #include "step_kernels.hpp"
@@ -23,7 +25,7 @@ namespace {
 using fw2::ntld;
 using fw2::ntst;
 
-constexpr int kTX = 64;             // tile columns
+constexpr int kTX = 64;             // tile columns, where not said
 
 // (W x H) window of a 2D array with corner (xs, ys), loaded into registers and
 // stored to LDS; cells outside the grid are zero (the array's halo corner).
@@ -87,28 +89,28 @@ __device__ __forceinline__ void store_memory(const float *m, float *f, const Geo
 // LDS of a pressure tile: v_x and v_y with the reach of D^- (4 cells before,
 // 3 after, 1 across) and the tile's sources; of a velocity tile: p with the
 // reach of D^+ (3 before, 4 after, 1 across).
-template <int TY>
+template <int TY, int TX = kTX>
 struct PressureLds {
-    static constexpr int XW = kTX + 7, XH = TY + 2, YW = kTX + 2, YH = TY + 7;
+    static constexpr int XW = TX + 7, XH = TY + 2, YW = TX + 2, YH = TY + 7;
     float x[XW * XH], y[YW * YH];
-    int src[kTX * TY];
+    int src[TX * TY];
 };
-template <int TY>
+template <int TY, int TX = kTX>
 struct VelocityLds {
-    static constexpr int PW = kTX + 7, PH = TY + 7;
+    static constexpr int PW = TX + 7, PH = TY + 7;
     float p[PW * PH];
 };
 
 // Pressure phase of the tile at (x0, y0).  s: sources to add, of step `step`
 // (s.n = 0: none).  All threads of the block call it.
-template <int L, bool CENTRED, bool PP, int TY>
+template <int L, bool CENTRED, bool PP, int TY, int TX>
 __device__ __forceinline__ void pressure_tile(const StepArgs &a, int x0, int y0, const SparseArgs &s, int n_src,
-                                              long long step, PressureLds<TY> &lds)
+                                              long long step, PressureLds<TY, TX> &lds)
 {
-    using T = PressureLds<TY>;
-    constexpr int NT = kTX * TY;
+    using T = PressureLds<TY, TX>;
+    constexpr int NT = TX * TY;
     const Geometry &g = a.geo;
-    const int tid = threadIdx.x, tx = tid % kTX, ty = tid / kTX, i = x0 + tx, j = y0 + ty;
+    const int tid = threadIdx.x, tx = tid % TX, ty = tid / TX, i = x0 + tx, j = y0 + ty;
     const int nx = g.n[0], ny = g.n[1];
     const bool live = i < nx && j < ny;
     const uint32_t pt = plane_point(g, i, j);
@@ -131,8 +133,8 @@ __device__ __forceinline__ void pressure_tile(const StepArgs &a, int x0, int y0,
         __syncthreads();
         for (int k = tid; k < n_src; k += NT) {
             const uint32_t f = (uint32_t)((const __attribute__((address_space(1))) int64_t *)s.idx)[k], y = f / (uint32_t)nx, x = f - y * (uint32_t)nx;
-            if (x - (uint32_t)x0 < (uint32_t)kTX && y - (uint32_t)y0 < (uint32_t)TY)
-                lds.src[(y - (uint32_t)y0) * kTX + (x - (uint32_t)x0)] = k + 1;
+            if (x - (uint32_t)x0 < (uint32_t)TX && y - (uint32_t)y0 < (uint32_t)TY)
+                lds.src[(y - (uint32_t)y0) * TX + (x - (uint32_t)x0)] = k + 1;
         }
     }
     wx.store(lds.x, tid);
@@ -180,13 +182,13 @@ __device__ __forceinline__ void pressure_tile(const StepArgs &a, int x0, int y0,
 }
 
 // Velocity phase of the tile at (x0, y0).
-template <int L, bool CENTRED, bool PP, int TY>
-__device__ __forceinline__ void velocity_tile(const StepArgs &a, int x0, int y0, VelocityLds<TY> &lds)
+template <int L, bool CENTRED, bool PP, int TY, int TX>
+__device__ __forceinline__ void velocity_tile(const StepArgs &a, int x0, int y0, VelocityLds<TY, TX> &lds)
 {
-    using T = VelocityLds<TY>;
-    constexpr int NT = kTX * TY;
+    using T = VelocityLds<TY, TX>;
+    constexpr int NT = TX * TY;
     const Geometry &g = a.geo;
-    const int tid = threadIdx.x, tx = tid % kTX, ty = tid / kTX, i = x0 + tx, j = y0 + ty;
+    const int tid = threadIdx.x, tx = tid % TX, ty = tid / TX, i = x0 + tx, j = y0 + ty;
     const int nx = g.n[0], ny = g.n[1];
     const bool live = i < nx && j < ny;
     const uint32_t pt = plane_point(g, i, j);

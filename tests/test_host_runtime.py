@@ -12,7 +12,7 @@ CSRC = os.path.join(ROOT, "paper_2106_11476_amd", "csrc")
 
 
 @pytest.mark.parametrize("driver", ["devices_driver.cpp", "workspace_driver.cpp", "sources_driver.cpp", "tiles_driver.cpp",
-                                    "limits_driver.cpp"])
+                                    "limits_driver.cpp", "bands_driver.cpp"])
 def test_host_routes(driver, tmp_path):
     from paper_2106_11476_amd import build
     exe = str(tmp_path / "driver")
