@@ -119,11 +119,12 @@ fw2_status validate_scalars(const fw2_domain_desc *d)
 // one step to the next.  Up to it the two-phase 2D tiles (all entries of a
 // batch together) read and write the memory variables by plain accesses, past
 // it by non-temporal ones, which leave the cache to the arrays that both
-// phases read.  Measured, us per step, plain / non-temporal: 1237 x 893, L = 8
-// (175 MB) 59.1 / 69.2; 1600^2, L = 4 (235 MB) 74.6 / 82.0; 2400 x 2300, L = 1
-// (249 MB) 81.1 / 92.0; 1700^2, L = 4 (261 MB) 100 / 95.6; 2000 x 1900, L = 3
-// (277 MB) 107 / 99.5; 4096 x 2048, L = 4 303 / 242.  The 3D sweeps keep the
-// hint: plain accesses gain 7% at 126^3 and lose from 140^3 on.
+// phases read.  Measured, us per step, plain / non-temporal, with the bytes of
+// all arrays as laid out: 1237 x 893, L = 8 (175 MB) 59.1 / 69.2; 2400 x 2300,
+// L = 1 (225 MB) 81.1 / 92.0; 1600^2, L = 4 (235 MB) 74.6 / 82.0; 1700^2, L = 4
+// (260 MB) 100 / 95.6; 2000 x 1900, L = 3 (281 MB) 107 / 99.5; 4096 x 2048, L = 4
+// (753 MB) 303 / 242: the line, 252 MB, lies between 235 and 260.  The 3D sweeps
+// keep the hint: plain accesses gain 7% at 126^3 and lose from 140^3 on.
 constexpr int64_t kCacheBytes = (int64_t)240 << 20;
 
 // 2D grids advanced by one launch a step, out of place (step_f2.hip; in a
@@ -131,7 +132,7 @@ constexpr int64_t kCacheBytes = (int64_t)240 << 20;
 // medium stay in the cache, and with more than two mechanisms only while every
 // 64 x 16 tile has a CU of its own.  Measured, us per step, two phases against
 // one launch: L = 2 128^2 6.4 / 5.0, 480^2 9.4 / 8.0, 1024^2 25.9 / 23.4,
-// 1536^2 (240 MB) 50.2 / 45.7, 1600^2 (267 MB) 53.7 / 55.0; L = 4 480^2 11.4 /
+// 1536^2 (247 MB) 50.2 / 45.7, 1600^2 (268 MB) 53.7 / 55.0; L = 4 480^2 11.4 /
 // 10.6; L = 3 600 x 500 12.5 / 12.4, 1024^2 31.0 / 31.1.
 bool one_launch_size(const fw2_domain_desc *d, int64_t stride)
 {
