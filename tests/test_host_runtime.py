@@ -11,14 +11,29 @@ HOST = os.path.join(ROOT, "tests", "host")
 CSRC = os.path.join(ROOT, "paper_2106_11476_amd", "csrc")
 
 
-@pytest.mark.parametrize("driver", ["devices_driver.cpp", "workspace_driver.cpp", "sources_driver.cpp", "tiles_driver.cpp",
-                                    "limits_driver.cpp", "bands_driver.cpp"])
-def test_host_routes(driver, tmp_path):
+def _compile(*args):
     from paper_2106_11476_amd import build
+    subprocess.check_call([build.hipcc(), "--cuda-host-only", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "include"),
+                           "-I", CSRC, "-I", HOST] + list(args))
+
+
+@pytest.fixture(scope="module")
+def host_objects(tmp_path_factory):
+    """The library's host code, compiled once for all drivers."""
+    out = tmp_path_factory.mktemp("host")
+    objects = []
+    for name in ("fw2.cpp", "setup.cpp"):
+        objects.append(str(out / (name + ".o")))
+        _compile("-c", os.path.join(CSRC, name), "-o", objects[-1])
+    return objects
+
+
+@pytest.mark.parametrize("driver", ["devices_driver.cpp", "workspace_driver.cpp", "sources_driver.cpp",
+                                    "tiles_driver.cpp", "limits_driver.cpp", "bands_driver.cpp"])
+def test_host_routes(driver, host_objects, tmp_path):
     exe = str(tmp_path / "driver")
-    subprocess.check_call([build.hipcc(), "-std=c++17", "-O1", "--offload-arch=gfx950", "-I", os.path.join(ROOT, "include"),
-                           "-I", CSRC, "-I", HOST, os.path.join(CSRC, "fw2.cpp"), os.path.join(CSRC, "setup.cpp"),
-                           os.path.join(HOST, driver), "-o", exe])
+    _compile("-c", os.path.join(HOST, driver), "-o", exe + ".o")
+    _compile(exe + ".o", *host_objects, "-o", exe)
     r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
     assert ": 0 failed" in r.stdout
