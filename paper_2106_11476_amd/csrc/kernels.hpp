@@ -123,6 +123,15 @@ __host__ __device__ inline int shifted_tile(int bid, int nblocks, int shift)
     return x * (nblocks / 8) + (x < rem ? x : rem) + (bid / 8 + x * shift) % count;
 }
 
+// Tile of block `bid` in plain order over rows of nbx tiles, each row starting
+// five tiles further on than the one before, so that a column of tiles does not
+// stay on one XCD.  A bijection of whole rows.
+__host__ __device__ inline int skewed_tile(int bid, int nbx)
+{
+    const int row = bid / nbx;
+    return row * nbx + (bid - row * nbx + 5 * row) % nbx;
+}
+
 // Many 2D domains advanced by one launch per phase (batched serving).  The
 // table lives in device memory; the blocks of a grid sized for the tiles of
 // all entries walk them, so a captured step loop does not depend on which

@@ -374,19 +374,31 @@ __device__ __forceinline__ void add_sources(const TileSources &t, const SparseAr
     }
 }
 
+// Arrays of a step past this size: where the number of tiles is no multiple of
+// 8, the 3D sweeps keep the plain order of tiles.  Bands (tile_of_block) share
+// halo lines in one XCD's L2, but stream from eight far places of every array.
+// us per step, bands / plain: L = 2 401 x 399 x 397 (5.6 GB) 2467 / 2262, 700 x 600 x
+// 300 4497 / 4240; L = 4 3737 / 3494 and 6846 / 6583, 900 x 300 x 300 4510 / 4290; L = 6
+// 300 x 200 x 100 (1.2 GB) 431 / 411; but L = 2 203 x 149 x 177 (0.6 GB) 209 / 224, L = 4
+// 300 x 200 x 100 (0.9 GB) 335 / 332.
+constexpr int64_t kPlainBytes = (int64_t)1 << 30;
+
+// Tile of block `bid`; bands = 0: plain order, else the number of tiles.
+__device__ __forceinline__ int tile_of_sweep(int bid, int bands) { return bands ? tile_of_block(bid, bands) : bid; }
+
 // PF: 0 -- every plane's loads issued in its own iteration; 1 -- all loads
 // of plane k + 1 issued during plane k; 2 -- only the staged planes and the
 // z window one plane ahead, the point's own values (medium, memory
 // variables) issued at the top of their own plane (fewer registers).
 template <int L, bool CENTRED, int BX, int BY, bool PP, int PF>
-__global__ void __launch_bounds__(BX *BY) pressure_sweep3d(const StepArgs a, int rows, int nbx, int nby, int nblocks)
+__global__ void __launch_bounds__(BX *BY) pressure_sweep3d(const StepArgs a, int rows, int nbx, int nby, int bands)
 {
     constexpr int NT = BX * BY;
     constexpr int XW = BX + 8, XH = BY + 2;     // v_x tile: x halo 4, y halo 1
     constexpr int YW = BX + 2, YH = BY + 8;     // v_y tile: x halo 1, y halo 4
     constexpr int ZW = BX + 2, ZH = BY + 2;     // v_z tile: halo 1
     const Geometry &g = a.geo;
-    const int tile = tile_of_block(blockIdx.x, nblocks);
+    const int tile = tile_of_sweep(blockIdx.x, bands);
     const int tx_ = tile % nbx, rest = tile / nbx;
     const int x0 = tx_ * BX, y0 = (rest % nby) * BY, z0 = (rest / nby) * rows;
     const int tid = threadIdx.x;
@@ -557,7 +569,7 @@ __global__ void __launch_bounds__(BX *BY) pressure_sweep3d(const StepArgs a, int
 }
 
 template <int L, bool CENTRED, int BX, int BY, bool PP, int PF>
-__global__ void __launch_bounds__(BX *BY) velocity_sweep3d(const StepArgs a, int rows, int nbx, int nby, int nblocks)
+__global__ void __launch_bounds__(BX *BY) velocity_sweep3d(const StepArgs a, int rows, int nbx, int nby, int bands)
 {
     // with receivers, block 0 records them and blocks 1.. take the tiles
     const int shift = a.rcv.step ? 1 : 0;
@@ -569,7 +581,7 @@ __global__ void __launch_bounds__(BX *BY) velocity_sweep3d(const StepArgs a, int
     constexpr int PW = BX + 8, PH = BY + 8;     // p tile: halo 4 (x0-4.., y0-4..)
     constexpr int RW = BX + 1, RH = BY + 1;     // rho / kappa0 tiles: +1 halo
     const Geometry &g = a.geo;
-    const int tile = tile_of_block((int)blockIdx.x - shift, nblocks);
+    const int tile = tile_of_sweep((int)blockIdx.x - shift, bands);
     const int tx_ = tile % nbx, rest = tile / nbx;
     const int x0 = tx_ * BX, y0 = (rest % nby) * BY, z0 = (rest / nby) * rows;
     const int tid = threadIdx.x;
@@ -733,6 +745,7 @@ __global__ void __launch_bounds__(BX *BY) velocity_sweep3d(const StepArgs a, int
 template <int L, bool C, bool PP, int PF>
 hipError_t launch_sweep3(const StepArgs &a, bool pressure, const KernelConfig &kc, hipStream_t st)
 {
+    const bool far = (7 + 6 * L) * a.geo.stride * 4 > kPlainBytes;      // arrays of a step: 3D state and medium
     // tile BX x BY: kc.bx selects 16 x 16, 32 x 16 or 64 x 8 (kc.by = 0), or
     // with kc.by the 256-thread tiles 64 x 4 and 32 x 8 (variant 3 only)
 #define FW2_SWEEP3(BXV, BYV, COND)                                                                      \
@@ -740,14 +753,14 @@ hipError_t launch_sweep3(const StepArgs &a, bool pressure, const KernelConfig &k
     if (kc.bx == BXV && (kc.by == 0 ? (BYV == (BXV == 64 ? 8 : 16)) : kc.by == BYV)) {                  \
         const int nbx = (a.geo.n[0] + BXV - 1) / BXV, nby = (a.geo.n[1] + BYV - 1) / BYV;                \
         const int nbz = (a.geo.n[2] + kc.rows - 1) / kc.rows;                                           \
-        const int nblocks = nbx * nby * nbz;                                                            \
+        const int nblocks = nbx * nby * nbz, bands = far && nblocks % 8 ? 0 : nblocks;                  \
         if (pressure)                                                                                   \
             hipLaunchKernelGGL((pressure_sweep3d<L, C, BXV, BYV, PP, PF>), dim3(nblocks), dim3(BXV * BYV), 0, st, \
-                               a, kc.rows, nbx, nby, nblocks);                                          \
+                               a, kc.rows, nbx, nby, bands);                                          \
         else                                                                                            \
             hipLaunchKernelGGL((velocity_sweep3d<L, C, BXV, BYV, PP, PF>), dim3(nblocks + (a.rcv.step ? 1 : 0)),   \
                                dim3(BXV * BYV), 0, st,                                                  \
-                               a, kc.rows, nbx, nby, nblocks);                                          \
+                               a, kc.rows, nbx, nby, bands);                                          \
         return hipGetLastError();                                                                       \
     }
     FW2_SWEEP3(32, 16, L <= 4)

@@ -6,19 +6,22 @@ namespace fw2 {
 
 namespace {
 
-// The tile of a block: the eight XCDs take a contiguous band each, and (4 rows,
-// band_shift) XCD x starts x * shift tiles into it.
+// The tile of a block by the launch's order of tiles: 0, each of the eight XCDs
+// takes a contiguous band of them; > 0, the same, XCD x starting x * order tiles
+// into its band (4 rows, band_shift); kSkewed, plain order, skewed by row.
+constexpr int kSkewed = -1;
 template <int TY>
-__device__ __forceinline__ int tile_of_band(int bid, int nblocks, int shift)
+__device__ __forceinline__ int tile_of(int bid, int nbx, int nblocks, int order)
 {
-    return TY == 4 && shift ? shifted_tile(bid, nblocks, shift) : tile_of_block(bid, nblocks);
+    if (order == kSkewed) return skewed_tile(bid, nbx);
+    return TY == 4 && order > 0 ? shifted_tile(bid, nblocks, order) : tile_of_block(bid, nblocks);
 }
 
 template <int L, bool C, bool PP, int TY, int TX>
-__global__ void __launch_bounds__(TX *TY) pressure_tiles(const StepArgs a, int nbx, int nblocks, int shift)
+__global__ void __launch_bounds__(TX *TY) pressure_tiles(const StepArgs a, int nbx, int nblocks, int order)
 {
     __shared__ PressureLds<TY, TX> lds;
-    const int tile = tile_of_band<TY>(blockIdx.x, nblocks, shift);
+    const int tile = tile_of<TY>(blockIdx.x, nbx, nblocks, order);
     long long step = 0;
     int n_src = 0;
     if (a.src.n > 0) {
@@ -29,7 +32,7 @@ __global__ void __launch_bounds__(TX *TY) pressure_tiles(const StepArgs a, int n
 }
 
 template <int L, bool C, bool PP, int TY, int TX>
-__global__ void __launch_bounds__(TX *TY) velocity_tiles(const StepArgs a, int nbx, int nblocks, int shift)
+__global__ void __launch_bounds__(TX *TY) velocity_tiles(const StepArgs a, int nbx, int nblocks, int order)
 {
     const int rcv = a.rcv.step ? 1 : 0;              // with receivers, block 0 records them
     if ((int)blockIdx.x < rcv) {
@@ -37,7 +40,7 @@ __global__ void __launch_bounds__(TX *TY) velocity_tiles(const StepArgs a, int n
         return;
     }
     __shared__ VelocityLds<TY, TX> lds;
-    const int tile = tile_of_band<TY>((int)blockIdx.x - rcv, nblocks, shift);
+    const int tile = tile_of<TY>((int)blockIdx.x - rcv, nbx, nblocks, order);
     velocity_tile<L, C, PP, TY, TX>(a, (tile % nbx) * TX, (tile / nbx) * TY, lds);
 }
 
@@ -70,19 +73,39 @@ int band_shift(const Geometry &g, int nbx, int nblocks)
     return apart * 100 >= (int64_t)3275 * 65536 && apart * 100 <= (int64_t)3303 * 65536 ? 3 * nbx : 0;
 }
 
+// Arrays of a step past kPlainBytes (two mechanisms or more): tiles in plain
+// order, skewed.  Bands keep the rows that neighbouring tiles share in one XCD's L2, but
+// then eight bands stream from eight far places of every array, and the further
+// past the last-level cache the arrays are, and the more of them are memory
+// variables, which nothing shares, the more that costs.  us per step, bands /
+// skewed (64 x 8 tiles; L = 6, 8: 128 x 4): L = 2 9000 x 2000 (968 MiB) 389 / 381,
+// 12000 x 2000 623 / 518, 10000 x 4000 900 / 839, but 8100 x 4000 665 / 713; L = 3
+// 3600^2 (904 MiB) 332 / 338, 6000 x 3000 508 / 480; L = 4 4096 x 2048 (718 MiB) 243 /
+// 260, 3000 x 4000 (1012) 356 / 364, 2500 x 5000 (1076) 399 / 388, 12000 x 2000 992 /
+// 757 (row sweeps, in plain order there, 792), 11900 x 2500 1129 / 943; L = 6 4096 x
+// 2048 (978) 335 / 350, 3072^2 (1105) 488 / 388; L = 8 3000^2 472 / 466.  L = 1 gains
+// and loses by as much (20000 x 2000 699 / 727, 30000 x 1200 635 / 608) and keeps
+// its bands.
+template <int L>
+int tile_order(const Geometry &g, int nbx, int nblocks, int rows)
+{
+    if (L >= 2 && (6 + 4 * L) * g.stride * 4 > kPlainBytes) return kSkewed;
+    return rows == 4 ? band_shift(g, nbx, nblocks) : 0;
+}
+
 template <int L, bool C, bool PP, int TY>
 hipError_t launch(const StepArgs &a, bool pressure, hipStream_t st)
 {
     constexpr int TX = TY == 4 ? kTX4 : kTX;
     constexpr unsigned reserve = TY == 4 ? kReserve4 : 0;
     const int nbx = (a.geo.n[0] + TX - 1) / TX, nblocks = nbx * ((a.geo.n[1] + TY - 1) / TY);
-    const int shift = TY == 4 ? band_shift(a.geo, nbx, nblocks) : 0;
+    const int order = tile_order<L>(a.geo, nbx, nblocks, TY);
     if (pressure)
         hipLaunchKernelGGL((pressure_tiles<L, C, PP, TY, TX>), dim3(nblocks), dim3(TX * TY), reserve, st, a, nbx, nblocks,
-                           shift);
+                           order);
     else
         hipLaunchKernelGGL((velocity_tiles<L, C, PP, TY, TX>), dim3(nblocks + (a.rcv.step ? 1 : 0)), dim3(TX * TY), reserve,
-                           st, a, nbx, nblocks, shift);
+                           st, a, nbx, nblocks, order);
     return hipGetLastError();
 }
 

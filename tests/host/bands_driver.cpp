@@ -1,4 +1,5 @@
-// The shifted tile order visits every tile once, XCD by XCD within its band.
+// The shifted and the skewed tile order visit every tile once: the one XCD by
+// XCD within its band, the other row by row.
 #include <cstdio>
 #include <vector>
 
@@ -18,6 +19,15 @@ int main()
             }
         }
     if (fw2::shifted_tile(8 * 5 + 2, 800, 7) != 200 + 5 + 14 || fw2::shifted_tile(8 * 99 + 1, 800, 7) != 100 + 6) ++bad;
+    for (int nbx = 1; nbx < 40; ++nbx)
+        for (int nby : {1, 2, 7, 30}) {
+            std::vector<int> seen(nbx * nby, 0);
+            for (int b = 0; b < nbx * nby; ++b) {
+                const int t = fw2::skewed_tile(b, nbx);
+                if (t / nbx != b / nbx || seen[t]++) ++bad;
+            }
+        }
+    if (fw2::skewed_tile(3 * 64 + 60, 64) != 3 * 64 + 11) ++bad;
     std::printf("bands: %d failed\n", bad);
     return bad ? 1 : 0;
 }

@@ -1,6 +1,6 @@
 """The 128 x 4 tiles of more than four mechanisms against the one-thread-per-
-point kernels, bit for bit: at their edges, and on grids whose bands of tiles
-start shifted (about 33 x 64 KiB apart) or, one size further, do not."""
+point kernels, bit for bit, at their edges; and grids on either side of the
+rules that order the tiles (bands, shifted bands, plain order)."""
 import numpy as np
 import pytest
 
@@ -49,12 +49,29 @@ def test_wide_tiles_at_their_edges(shape, L, scheme, local, monkeypatch):
         assert np.array_equal(ref[k], got[k]), k
 
 
-@pytest.mark.parametrize("shape", [(2048, 2048), (1900, 2252), (2048, 2112)])
-def test_bands_of_tiles_equal_the_per_point_kernels(shape, monkeypatch):
+# shifted bands, bands, and past 1 GiB of arrays (the first and the last grid
+# on either side, and a wide one) plain order
+@pytest.mark.parametrize("shape,L", [((2048, 2048), 5), ((1900, 2252), 5), ((2048, 2112), 5), ((3072, 3882), 4),
+                                     ((3072, 3883), 4), ((12000, 1700), 2), ((2048, 3400), 8)])
+def test_orders_of_tiles_equal_the_per_point_kernels(shape, L, monkeypatch):
     _torch()
-    prob = _problem(shape, 5, 1, 0, 30)
-    state = dict(zip(("p", "v", "psi1", "psi2"), W.random_state(2, 5, shape, seed=4)))
-    _say("bands of tiles", shape)
+    prob = _problem(shape, L, 1, 0, 30)
+    state = dict(zip(("p", "v", "psi1", "psi2"), W.random_state(2, L, shape, seed=4)))
+    _say("order of tiles", shape, "L", L)
     ref, got = (_run(prob, state, c, monkeypatch, 3) for c in ("0,64,8", None))
     for k in ref:
         assert np.array_equal(ref[k], got[k]), k
+
+
+@pytest.mark.parametrize("shape,L,banded", [((300, 200, 100), 6, "3,64,13"), ((330, 220, 126), 4, "3,64,16")])
+def test_orders_of_3d_tiles_give_the_same_bits(shape, L, banded, monkeypatch):
+    """Past 1 GiB of arrays and with a tile count that is no multiple of 8, the
+    3D sweeps take their tiles in plain order; 5 x 25 x 8 and 6 x 28 x 8 tiles
+    go in bands."""
+    _torch()
+    prob = _problem(shape, L, 1, 0, 30)
+    state = dict(zip(("p", "v", "psi1", "psi2"), W.random_state(3, L, shape, seed=4)))
+    _say("order of 3D tiles", shape, "L", L)
+    ref, got, plain = (_run(prob, state, c, monkeypatch, 3) for c in (banded, None, "3,64,11"))
+    for k in ref:
+        assert np.array_equal(ref[k], got[k]) and np.array_equal(ref[k], plain[k]), k
